@@ -236,7 +236,7 @@ def kernel_class(name):
     """Timer class of a kernel from its name in a trace: the bf16 GEMM and
     split-K epilogue instantiations carry their projection as the first
     template argument."""
-    m = re.search(r"(?:gemm_bf16_nt|splitk_epilogue)<(\d+)", name)
+    m = re.search(r"(?:gemm_bf16_nt|gemm_ring|splitk_epilogue)<(\d+)", name)
     if m:
         return GEMM_CLASSES[int(m.group(1))]
     if re.search(r"ln_mod_bf16<\d+, true>", name) or "pack_rows" in name:

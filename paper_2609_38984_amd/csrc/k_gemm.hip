@@ -11,126 +11,19 @@
 // Epilogues (bias, tanh-GELU, gated residual) are fused into the store.
 // Split K: when the output tiles cannot fill the 256 CUs (few rows, or a
 // narrow N), grid.y workgroups share a tile along K, store fp32 partial sums,
-// and one memory-bound pass sums them and applies the epilogue.
+// and one memory-bound pass sums them and applies the epilogue (or the
+// epilogue and the LayerNorm that follows: launch_splitk_ln).
+// Short token sets run the ring kernel of k_ring.hip instead (plan_gemm).
+#include "gemm_common.h"
 #include "score_unit.h"
 
 #include <algorithm>
 
 namespace swam {
 
-__device__ __forceinline__ float gelu_tanh(float u) {
-  // 0.5 u (1 + tanh(z)) = u / (1 + exp(-2 z)), z = sqrt(2/pi) (u + 0.044715 u^3);
-  // exp(-2z) = exp2(-2 log2(e) z) on the hardware exp2, then the hardware reciprocal
-  // (both about 1 ulp: far below the bf16 rounding of the stored result)
-  const float z2 = -2.0f * 1.4426950408889634f * 0.7978845608028654f *
-                   (u + 0.044715f * u * u * u);
-  return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z2));
-}
-
-template <int EPI>
-__device__ __forceinline__ float epi_value(float acc, float bias, float gate, float resid) {
-  if (EPI == EPI_BIAS) return acc + bias;
-  if (EPI == EPI_BIAS_GELU) return gelu_tanh(acc + bias);
-  return resid + gate * (acc + bias);
-}
-
-// Store of 8 consecutive QKV columns of one row with the QK-norm / rotary
-// embedding of q and k heads applied (the steps of qk_post_kernel on the
-// projection rounded to bf16).  The 8 lanes storing one row's 64 columns are
-// consecutive and aligned, and a wave's 64 columns are one head, so the head
-// norm is a 3-step exchange; every lane takes part (the store is guarded).
-__device__ __forceinline__ void qkpost_store(const float* v, const bf16_t* __restrict__ bias,
-                                             bf16_t* C, int64_t ldc, int row, int col, int col0,
-                                             int M, int N, const QkPost& qp) {
-  float x[8];
-  {
-    const float4 v0 = *reinterpret_cast<const float4*>(v);
-    const float4 v1 = *reinterpret_cast<const float4*>(v + 4);
-    const float a[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-    uint4 bw = make_uint4(0u, 0u, 0u, 0u);
-    if (col < N) bw = *reinterpret_cast<const uint4*>(bias + col);
-    const uint32_t bb[4] = {bw.x, bw.y, bw.z, bw.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      // the projection is stored (rounded to bf16) before the post-processing
-      x[2 * e] = bf16_to_f32(f32_to_bf16(a[2 * e] + __uint_as_float(bb[e] << 16)));
-      x[2 * e + 1] = bf16_to_f32(f32_to_bf16(a[2 * e + 1] + __uint_as_float(bb[e] & 0xFFFF0000u)));
-    }
-  }
-  if (col0 < 2 * qp.d) {                      // q or k head (wave-uniform)
-    if (qp.qk_norm) {
-      float ss = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
-      ss += __shfl_xor(ss, 1);
-      ss += __shfl_xor(ss, 2);
-      ss += __shfl_xor(ss, 4);
-      const float r = rsqrtf(ss / 64.0f + 1e-6f);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] *= r;
-    }
-    if (qp.tab != nullptr) {
-      const int rr = min(row, M - 1);
-      int pos;
-      if (qp.pos_mode == 0) {
-        pos = rr % qp.l_full;
-      } else if (qp.pos_mode == 1) {
-        pos = qp.gather[rr] % qp.l_full;
-      } else {
-        int b = 0;
-        while (b + 1 < qp.n_seqs && qp.cu[b + 1] <= rr) ++b;
-        pos = rr - qp.cu[b];
-      }
-      pos = min(max(pos, 0), qp.n_pos - 1);
-      const float2* t = qp.tab + (int64_t)pos * 32 + ((col & 63) >> 1);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float2 cs = t[e];
-        const float a = x[2 * e], b = x[2 * e + 1];
-        x[2 * e] = a * cs.x - b * cs.y;
-        x[2 * e + 1] = a * cs.y + b * cs.x;
-      }
-    }
-  }
-  if (row < M && col < N)
-    *reinterpret_cast<uint4*>(C + (int64_t)row * ldc + col) =
-        make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]),
-                   pack_bf16x2(x[6], x[7]));
-}
-
 // ---------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ---------------------------------------------------------------------------
-constexpr int GEMM_BK = 64;
-constexpr int GROUP_M = 8;
-
-__device__ __forceinline__ void tile_of(int pid, int nwg, int tiles_m, int tiles_n, int& tm,
-                                        int& tn) {
-  // XCD remap: ids with equal (pid % 8) run on one XCD; give them consecutive ids.
-  const int xcd = pid & 7;
-  const int per = nwg >> 3, rem = nwg & 7;
-  const int id = xcd * per + min(xcd, rem) + (pid >> 3);
-  const int in_group = GROUP_M * tiles_n;
-  const int group = id / in_group;
-  const int first_m = group * GROUP_M;
-  const int gsz = min(tiles_m - first_m, GROUP_M);
-  tm = first_m + (id % in_group) % gsz;
-  tn = (id % in_group) / gsz;
-}
-
-typedef __attribute__((address_space(3))) void lds_void_t;
-
-// dword 3 of a raw buffer descriptor on gfx9-family parts (32-bit data format)
-constexpr int SWAM_BUF_DWORD3 = 0x00020000;
-
-// per-lane offset + wave-uniform step, formed at the point of use: an asm add
-// keeps the compiler from hoisting one live VGPR per slab out of the k loop
-__device__ __forceinline__ int vadd_sgpr(int v, int s) {
-  int r;
-  asm volatile("v_add_u32 %0, %1, %2" : "=v"(r) : "s"(s), "v"(v));
-  return r;
-}
-
 // one k-stage (64) of MFMAs from a staged A/B tile pair.  The operand
 // fragments of k-step s + 1 are read from LDS while the MFMAs of k-step s
 // run (two fragment sets), and the schedule interleaves one LDS read after
@@ -532,12 +425,6 @@ static hipError_t run_bf16(const void* A, int64_t lda, const void* B, int64_t ld
                        dim3(WM * WN * 64), 0, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb,
                        (const bf16_t*)bias, gate, (bf16_t*)C, ldc, M, N, K, tiles_m, tiles_n, part,
                        QkPost{}, ScoreArgs{}, 0, (bf16_t*)nullptr, (const int32_t*)nullptr);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t n = (int64_t)M * (N / 8);
-    hipLaunchKernelGGL((splitk_epilogue<ROLE, EPI>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                       part, splits, M, N, (const bf16_t*)bias, gate, (bf16_t*)C, ldc,
-                       (bf16_t*)Cs, smap);
     return hipGetLastError();
   }
 }
@@ -564,7 +451,7 @@ static hipError_t run_bf16(const void* A, int64_t lda, const void* B, int64_t ld
 // slower than the three K slices.  (A 256x128 tile measured at 0.72 of the
 // base rate never won at any block shape from d = 256 to 4096 and was
 // dropped.)
-struct GemmPlan { int tile, splits; };
+struct GemmPlan { int tile, splits; bool ring; double us; };
 constexpr int GEMM_TILES = 4;
 static const int TILE_BM[GEMM_TILES] = {256, 128, 192, 192};
 static const int TILE_BN[GEMM_TILES] = {256, 128, 256, 128};
@@ -577,7 +464,7 @@ static GemmPlan choose_gemm(int64_t M, int64_t N, int64_t K, int64_t ws_floats,
   const int split_opts[6] = {1, 2, 3, 4, 6, 8};
   const int64_t kt = K / GEMM_BK;
   const double cu_flops = 2.5e15 / 256.0 * 0.40;        // sustained MFMA rate per CU
-  GemmPlan best{0, 1};
+  GemmPlan best{0, 1, false, 0.0};
   double best_t = 1e30;
   for (int i = 0; i < GEMM_TILES; ++i) {
     if (wide_only && i == 3) continue;
@@ -598,26 +485,93 @@ static GemmPlan choose_gemm(int64_t M, int64_t N, int64_t K, int64_t ws_floats,
       double t = rounds * 2.0 * bm * bn * per_cu * k_slice /
                  (cu_flops * eff[i]);
       if (s > 1) t += ((double)s * M * N * 4.0 + 4.0 * M * N) / 4.0e12 + 3e-6;
-      if (t < best_t) { best_t = t; best = {i, s}; }
+      if (t < best_t) { best_t = t; best = {i, s, false, 0.0}; }
+    }
+  }
+  // launch and pipeline fill on top of the model above (the fit of choose_ring)
+  best.us = 0.945e6 * best_t + 6.6;
+  return best;
+}
+
+// The ring kernel's time for a plan: 256 CUs take `n` workgroups each (two
+// share a CU's loads, so n counts them all), a workgroup costs a fill plus a
+// step per 64 columns of K (a fifth more once the CUs run out of step), and
+// split partial sums a pass of their own (shorter when the pass is the
+// LayerNorm launch that follows anyway).  The constants are a fit to 350
+// shapes with the weights read cold (M 64 .. 10,200, d 384 .. 2,048): choosing
+// by the two models runs within 0.5% of the best measured plan on average
+// (d = 1536, 192 rows: 11.0 / 10.7 / 14.0 / 17.7 us for QKV / out / up / down
+// against 19.5 / 14.6 / 23.0 / 21.6 of the tile kernels, which win from about
+// 1,000 rows at d = 1536, down projections from about 3,000).
+constexpr int RING_BM[RING_TILES] = {64, 64, 128, 128};
+constexpr int RING_BN[RING_TILES] = {64, 128, 64, 128};
+static GemmPlan choose_ring(int64_t M, int64_t N, int64_t K, int64_t ws_floats, bool ln_follows,
+                            int max_splits) {
+  const double t0[RING_TILES] = {4.0, 4.8, 4.8, 1.5}, fill[RING_TILES] = {0.33, 0.17, 0.19, 3.5},
+               step[RING_TILES] = {0.215, 0.392, 0.392, 0.51};
+  const int split_opts[6] = {1, 2, 3, 4, 6, 8};
+  const int64_t kt = K / GEMM_BK;
+  GemmPlan best{0, 1, true, 1e30};
+  for (int i = 0; i < RING_TILES; ++i) {
+    const int64_t tiles = ((M + RING_BM[i] - 1) / RING_BM[i]) * ((N + RING_BN[i] - 1) / RING_BN[i]);
+    for (int s : split_opts) {
+      if (s > max_splits || (s > 1 && (kt / s < 4 || (int64_t)s * M * N > ws_floats))) continue;
+      const int64_t n = (tiles * s + 255) / 256;
+      double us = t0[i] + n * (fill[i] + step[i] * (double)((kt + s - 1) / s)) * (n > 1 ? 1.21 : 1.0);
+      if (s > 1)
+        us += (ln_follows ? 0.5 : 3.0) + ((double)s * M * N * 4.85 + 4.0 * M * N) / 4.0e6;
+      if (us < best.us) best = {i, s, true, us};
     }
   }
   return best;
 }
 
+// the plan of one bf16 projection; ln_follows: a LayerNorm of the result is
+// next (out and down projections)
+static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t ws_floats, bool ln_follows) {
+  const GemmPlan c = choose_gemm(M, N, K, ws_floats);
+  const GemmPlan r = choose_ring(M, N, K, ws_floats, ln_follows, 8);
+  return r.us < c.us ? r : c;
+}
+
+template <int ROLE, int EPI>
+static hipError_t run_epilogue(const float* ws, int splits, int M, int N, const void* bias,
+                               const float* gate, void* C, int64_t ldc, void* Cs,
+                               const int32_t* smap, hipStream_t st) {
+  const int64_t n = (int64_t)M * (N / 8);
+  hipLaunchKernelGGL((splitk_epilogue<ROLE, EPI>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                     ws, splits, M, N, (const bf16_t*)bias, gate, (bf16_t*)C, ldc, (bf16_t*)Cs, smap);
+  return hipGetLastError();
+}
+
+// ln (out and down projections): a LayerNorm of the result into ln->h follows;
+// it shares the pass that sums the splits when K is split
 template <int ROLE, int EPI>
 static hipError_t dispatch_bf16(const void* A, int64_t lda, const void* B, int64_t ldb,
                                 const void* bias, const float* gate, void* C, int64_t ldc,
                                 int M, int N, int K, float* ws, int64_t ws_floats,
                                 hipStream_t st, void* Cs = nullptr,
-                                const int32_t* smap = nullptr) {
-  const GemmPlan p = choose_gemm(M, N, K, ws ? ws_floats : 0);
-  if (p.tile == 0)
-    return run_bf16<ROLE, 256, 256, 2, 4, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
-  if (p.tile == 2)
-    return run_bf16<ROLE, 192, 256, 2, 4, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
-  if (p.tile == 3)
-    return run_bf16<ROLE, 192, 128, 2, 4, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
-  return run_bf16<ROLE, 128, 128, 2, 2, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
+                                const int32_t* smap = nullptr, LnNext* ln = nullptr) {
+  const GemmPlan p = plan_gemm(M, N, K, ws ? ws_floats : 0, ln != nullptr);
+  hipError_t e;
+  if (p.ring) {
+    const RingArgs a{A, lda, B, ldb, bias, gate, C, ldc, M, N, K, ws, QkPost{}, Cs, smap};
+    e = launch_ring(ROLE, a, {p.tile, p.splits}, st);
+  } else if (p.tile == 0) {
+    e = run_bf16<ROLE, 256, 256, 2, 4, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
+  } else if (p.tile == 2) {
+    e = run_bf16<ROLE, 192, 256, 2, 4, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
+  } else if (p.tile == 3) {
+    e = run_bf16<ROLE, 192, 128, 2, 4, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
+  } else {
+    e = run_bf16<ROLE, 128, 128, 2, 2, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
+  }
+  if (e != hipSuccess) return e;
+  if (p.splits <= 1) return hipSuccess;
+  if (ln == nullptr)
+    return run_epilogue<ROLE, EPI>(ws, p.splits, M, N, bias, gate, C, ldc, Cs, smap, st);
+  ln->done = true;
+  return launch_splitk_ln(ws, p.splits, M, N, bias, gate, C, ln->h, ln->shift, ln->scale, st);
 }
 
 // The MLP up projection with one layer's scoring in the tail of its grid:
@@ -625,6 +579,7 @@ static hipError_t dispatch_bf16(const void* A, int64_t lda, const void* B, int64
 // round, on the CUs its tiles leave idle there (at least 16 of them, or the
 // caller scores on its side stream instead).
 static int scored_idle_slots(const GemmPlan& p, int64_t M, int64_t N) {
+  if (p.ring) return 0;
   const int bm = TILE_BM[p.tile], bn = TILE_BN[p.tile];
   if (p.splits != 1) return 0;
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -633,9 +588,17 @@ static int scored_idle_slots(const GemmPlan& p, int64_t M, int64_t N) {
   return idle >= 16 ? (int)idle : 0;
 }
 
+// the plan of a scored up projection: the ring kernel has no scoring tail, so
+// it is taken only where it saves more than the events that the scoring on
+// the side stream needs instead (about 8 us)
+static GemmPlan plan_up_scored(int64_t M, int64_t N, int64_t K, int64_t ws_floats) {
+  const GemmPlan p = plan_gemm(M, N, K, ws_floats, false), c = choose_gemm(M, N, K, ws_floats);
+  return p.ring && scored_idle_slots(c, M, N) > 0 && c.us < p.us + 8.0 ? c : p;
+}
+
 int gemm_up_scored_slots(int64_t M, int64_t N, int64_t K, int64_t ws_floats) {
   if (M <= 0) return 0;
-  return scored_idle_slots(choose_gemm(M, N, K, ws_floats), M, N);
+  return scored_idle_slots(plan_up_scored(M, N, K, ws_floats), M, N);
 }
 
 template <int BM, int BN, int WM, int WN>
@@ -660,7 +623,7 @@ hipError_t launch_gemm_up_scored(const void* A, int64_t lda, const void* B, int6
                                  int64_t K, const ScoreArgs& sa, hipStream_t st,
                                  int64_t ws_floats) {
   if (M <= 0) return hipSuccess;
-  const GemmPlan p = choose_gemm(M, N, K, ws_floats);
+  const GemmPlan p = plan_up_scored(M, N, K, ws_floats);
   const int n_sw = scored_idle_slots(p, M, N);
   if (n_sw == 0) return hipErrorNotSupported;
   const int m = (int)M, n = (int)N, k = (int)K;
@@ -683,8 +646,11 @@ static hipError_t run_f32(const void* A, int64_t lda, const void* B, int64_t ldb
 hipError_t launch_gemm(int dtype, int role, const void* A, int64_t lda, const void* B,
                        int64_t ldb, const void* bias, const float* gate, void* C,
                        int64_t ldc, int64_t M, int64_t N, int64_t K, hipStream_t st,
-                       float* ws, int64_t ws_floats, void* Cs, const int32_t* smap) {
+                       float* ws, int64_t ws_floats, void* Cs, const int32_t* smap,
+                       LnNext* ln) {
   if (M <= 0) return hipSuccess;
+  if (ln != nullptr && ((role != ROLE_OUT && role != ROLE_DOWN) || smap != nullptr || ldc != N))
+    return hipErrorNotSupported;             // LayerNorm of the plain residual stream only
   const int m = (int)M, n = (int)N, k = (int)K;
   if (smap != nullptr && (dtype != 1 || (role != ROLE_OUT && role != ROLE_DOWN) || Cs == nullptr))
     return hipErrorNotSupported;             // row scatter: bf16 gated-residual stores only
@@ -692,8 +658,8 @@ hipError_t launch_gemm(int dtype, int role, const void* A, int64_t lda, const vo
     switch (role) {
       case ROLE_QKV: return dispatch_bf16<ROLE_QKV, EPI_BIAS>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, st);
       case ROLE_UP: return dispatch_bf16<ROLE_UP, EPI_BIAS_GELU>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, st);
-      case ROLE_OUT: return dispatch_bf16<ROLE_OUT, EPI_BIAS_GATED_RESIDUAL>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, st, Cs, smap);
-      case ROLE_DOWN: return dispatch_bf16<ROLE_DOWN, EPI_BIAS_GATED_RESIDUAL>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, st, Cs, smap);
+      case ROLE_OUT: return dispatch_bf16<ROLE_OUT, EPI_BIAS_GATED_RESIDUAL>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, st, Cs, smap, ln);
+      case ROLE_DOWN: return dispatch_bf16<ROLE_DOWN, EPI_BIAS_GATED_RESIDUAL>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, st, Cs, smap, ln);
       default: return hipErrorInvalidValue;
     }
   }
@@ -714,8 +680,13 @@ hipError_t launch_gemm_qkv(int dtype, const void* A, int64_t lda, const void* B,
   const bool post = qp.qk_norm || qp.tab != nullptr;
   if (dtype == 1 && post) {
     const GemmPlan p = choose_gemm(M, N, K, ws ? ws_floats : 0, true);
+    const int m = (int)M, n = (int)N, k = (int)K;
+    const GemmPlan r = choose_ring(M, N, K, 0, false, 1);
+    if (r.us < p.us) {
+      const RingArgs a{A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, nullptr, qp, nullptr, nullptr};
+      return launch_ring(ROLE_QKV, a, {r.tile, 1}, st);
+    }
     if (p.splits <= 1) {
-      const int m = (int)M, n = (int)N, k = (int)K;
       if (p.tile == 0)
         return run_bf16<ROLE_QKV, 256, 256, 2, 4, EPI_BIAS_QKPOST>(A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, 1, nullptr, st, qp);
       if (p.tile == 2)

@@ -147,6 +147,101 @@ ln_mod_bf16(const bf16_t* __restrict__ x, bf16_t* __restrict__ h,
   }
 }
 
+// Sum of split-K partial rows, gated residual and the LayerNorm behind it: one
+// workgroup per row, thread t holding the 8-column chunks t, t + blockDim, ...
+// (up to CH), all partial loads of a chunk issued together.  Latency-bound at
+// the row counts that split K (a few hundred): one row per workgroup spreads
+// them over all CUs, and the pass replaces an epilogue pass and a LayerNorm
+// pass (192 x 1536, 6 slices: 4.9 us against 4.7 + 4.7).
+template <int CH>
+__global__ void __launch_bounds__(256)
+splitk_ln_bf16(const float* __restrict__ part, int splits, int64_t slice,
+               const bf16_t* __restrict__ bias, const float* __restrict__ gate,
+               bf16_t* __restrict__ x, bf16_t* __restrict__ h, const float* __restrict__ shift,
+               const float* __restrict__ scale, int d) {
+  __shared__ float red[2][4];
+  const int64_t row = blockIdx.x;
+  const int nch = d >> 3, tid = threadIdx.x, wave = tid >> 6, nw = blockDim.x >> 6;
+  float v[CH][8];
+  float s = 0.0f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int ci = tid + (int)blockDim.x * c;
+    if (ci >= nch) continue;
+    const int col = ci * 8;
+    const uint4 bw = *reinterpret_cast<const uint4*>(bias + col);
+    const uint4 xw = *reinterpret_cast<const uint4*>(x + row * d + col);
+    const float4 ga = *reinterpret_cast<const float4*>(gate + col);
+    const float4 gb = *reinterpret_cast<const float4*>(gate + col + 4);
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const float* p = part + row * d + col;
+#pragma unroll 4
+    for (int z = 0; z < splits; ++z) {
+      const float4 a = *reinterpret_cast<const float4*>(p + z * slice);
+      const float4 b = *reinterpret_cast<const float4*>(p + z * slice + 4);
+      acc[0] += a.x; acc[1] += a.y; acc[2] += a.z; acc[3] += a.w;
+      acc[4] += b.x; acc[5] += b.y; acc[6] += b.z; acc[7] += b.w;
+    }
+    const uint32_t bb[4] = {bw.x, bw.y, bw.z, bw.w}, xx[4] = {xw.x, xw.y, xw.z, xw.w};
+    const float gg[8] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z, gb.w};
+    uint32_t o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = __uint_as_float(xx[e] << 16) + gg[2 * e] * (acc[2 * e] + __uint_as_float(bb[e] << 16));
+      const float hi = __uint_as_float(xx[e] & 0xFFFF0000u) +
+                       gg[2 * e + 1] * (acc[2 * e + 1] + __uint_as_float(bb[e] & 0xFFFF0000u));
+      o[e] = pack_bf16x2(lo, hi);
+      // the LayerNorm reads the stored (rounded) row
+      v[c][2 * e] = __uint_as_float(o[e] << 16);
+      v[c][2 * e + 1] = __uint_as_float(o[e] & 0xFFFF0000u);
+      s += v[c][2 * e] + v[c][2 * e + 1];
+    }
+    *reinterpret_cast<uint4*>(x + row * d + col) = make_uint4(o[0], o[1], o[2], o[3]);
+  }
+  auto block_sum = [&](float t, float* r) {
+    t = warp_sum(t);
+    if ((tid & 63) == 0) r[wave] = t;
+    __syncthreads();
+    float u = r[0];
+    for (int w = 1; w < nw; ++w) u += r[w];
+    return u;
+  };
+  const float mean = block_sum(s, red[0]) / d;
+  float q = 0.0f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+    if (tid + (int)blockDim.x * c < nch)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { const float t = v[c][e] - mean; q += t * t; }
+  const float rstd = rsqrtf(block_sum(q, red[1]) / d + 1e-6f);
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int ci = tid + (int)blockDim.x * c;
+    if (ci >= nch) continue;
+    const int col = ci * 8;
+    uint32_t o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      o[e] = pack_bf16x2((v[c][2 * e] - mean) * rstd * (1.0f + scale[col + 2 * e]) + shift[col + 2 * e],
+                         (v[c][2 * e + 1] - mean) * rstd * (1.0f + scale[col + 2 * e + 1]) + shift[col + 2 * e + 1]);
+    *reinterpret_cast<uint4*>(h + row * d + col) = make_uint4(o[0], o[1], o[2], o[3]);
+  }
+}
+
+hipError_t launch_splitk_ln(const float* part, int splits, int64_t rows, int d, const void* bias,
+                            const float* gate, void* x, void* h, const float* shift,
+                            const float* scale, hipStream_t st) {
+  if (rows <= 0) return hipSuccess;
+  const int nt = d <= 512 ? 64 : d <= 1024 ? 128 : d <= 1536 ? 192 : 256;
+#define SWAM_SLN(CH_)                                                                          \
+  hipLaunchKernelGGL(splitk_ln_bf16<CH_>, dim3((unsigned)rows), dim3(nt), 0, st, part, splits, \
+                     rows * d, (const bf16_t*)bias, gate, (bf16_t*)x, (bf16_t*)h, shift, scale, d)
+  if (d <= 2048) SWAM_SLN(1);
+  else SWAM_SLN(2);                                // d <= 4096 (bf16 limit)
+#undef SWAM_SLN
+  return hipGetLastError();
+}
+
 // fp32 rows: two passes over global memory (rows are L1/L2 resident);
 // gather != NULL: as the bf16 GATHER variant
 __global__ void __launch_bounds__(256)

@@ -1,0 +1,275 @@
+// Projections of short token sets: C = epi(A . B^T + bias), M up to a few
+// thousand rows, bf16.
+//
+// What bounds these is not the matrix cores but the read of the weights (a
+// 192-row block of d = 1536 does 10.9 GFLOP on 57 MB of weights): a two-stage
+// tile loop waits out one memory round trip per 64 columns of K with 16 KB in
+// flight per workgroup.  Here the A and B tiles of NST k-stages of 64 form a
+// ring in LDS; the DMA loads of stage kt + NST - 1 are issued before stage kt
+// is multiplied and a counted vmcnt wait leaves the NST - 2 younger stages in
+// flight, so 48-128 KB per CU are on their way at any time.
+//
+// Tile (64 WM) x (64 WN): every wave holds a 64 x 64 accumulator block (four
+// 32x32x16 MFMAs per 16 columns of K) and the WK waves of one block take
+// different 16-column slices of each stage, so no operand fragment is read by
+// two waves of a block; their sums meet in LDS in a fixed order in the
+// epilogue.
+// `splits` > 1: that many workgroups share a tile along K and store fp32
+// partial sums (EPI_PARTIAL) for splitk_epilogue or splitk_ln.
+#include "gemm_common.h"
+
+#include <algorithm>
+
+namespace swam {
+
+// wait until at most V vector-memory operations and no LDS operation of this
+// wave are outstanding (vmcnt in bits 3:0 and 15:14, lgkmcnt in bits 11:8);
+// the empty asm statements keep the compiler's memory operations on their side
+template <int V>
+__device__ __forceinline__ void wait_stage() {
+  static_assert(V >= 0 && V < 64, "vmcnt is a 6-bit counter");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((V & 15) | (7 << 4) | ((V >> 4) << 14));
+  asm volatile("" ::: "memory");
+}
+
+// one DMA instruction: 16 bytes per lane from the buffer at `off` to a 1 KB LDS slab
+__device__ __forceinline__ void dma_slab(__amdgpu_buffer_rsrc_t r, uint4* slab, int off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)slab, 16, off, 0, 0, 0);
+}
+
+template <int ROLE, int WM, int WN, int WK, int NST, int EPI>
+__global__ void __launch_bounds__(WM * WN * WK * 64)
+gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ B, int64_t ldb,
+          const bf16_t* __restrict__ bias, const float* __restrict__ gate, bf16_t* C, int64_t ldc,
+          int M, int N, int K, int tiles_m, int tiles_n, int splits, float* __restrict__ part,
+          const QkPost qp, bf16_t* Cs, const int32_t* __restrict__ smap) {
+  constexpr int NW = WM * WN * WK, BM = 64 * WM, BN = 64 * WN;
+  constexpr int A_INS = BM / 8 / NW, B_INS = BN / 8 / NW, INS = A_INS + B_INS;
+  static_assert(A_INS * 8 * NW == BM && B_INS * 8 * NW == BN, "tile/waves mismatch");
+  static_assert(4 % WK == 0, "the waves of a block split the four k-steps of a stage");
+  constexpr int STAGE = (BM + BN) * 8;
+  constexpr int EP_LD = 68;                           // fp32 row pitch of a staged 32 x 64 slice
+  constexpr int RING = NST * STAGE, EPI_SLOTS = NW * 32 * EP_LD / 4;
+  __shared__ uint4 ring[RING > EPI_SLOTS ? RING : EPI_SLOTS];   // [stage][A rows | B rows][8 chunks]
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / (WK * WN);
+  const int n_tiles = tiles_m * tiles_n;
+  // consecutive ids per XCD, K slices slowest: the row tiles that read the
+  // same weights run on one XCD
+  const int nwg = n_tiles * splits, pid = blockIdx.x;
+  const int xcd = pid & 7, per = nwg >> 3, rem = nwg & 7;
+  const int id = xcd * per + min(xcd, rem) + (pid >> 3);
+  const int z = id / n_tiles, t = id - z * n_tiles;
+  const int in_group = GROUP_M * tiles_n, group = t / in_group, first_m = group * GROUP_M;
+  const int gsz = min(tiles_m - first_m, GROUP_M);
+  const int tm = first_m + (t % in_group) % gsz, tn = (t % in_group) / gsz;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int KT_all = K / GEMM_BK;
+  const int kt0 = KT_all * z / splits;
+  const int KT = KT_all * (z + 1) / splits;
+
+  // descriptors end with the tile's last valid row: rows of a ragged tile read
+  // as zeros, and so does every load of a stage past KT (offset DEAD)
+  constexpr int DEAD = 0x40000000;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(A + (int64_t)m0 * lda), (short)0, (int)(min(M - m0, BM) * lda * 2), SWAM_BUF_DWORD3);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(B + (int64_t)n0 * ldb), (short)0, (int)(min(N - n0, BN) * ldb * 2), SWAM_BUF_DWORD3);
+  const int lrow = lane >> 3;
+  int va[A_INS], vb[B_INS];
+#pragma unroll
+  for (int j = 0; j < A_INS; ++j) {
+    const int r = (wave * A_INS + j) * 8 + lrow;
+    va[j] = (int)((r * lda + 8 * ((lane & 7) ^ lds_swz(r))) * 2);
+  }
+#pragma unroll
+  for (int j = 0; j < B_INS; ++j) {
+    const int r = (wave * B_INS + j) * 8 + lrow;
+    vb[j] = (int)((r * ldb + 8 * ((lane & 7) ^ lds_swz(r))) * 2);
+  }
+  auto issue = [&](int slot, int kt) {
+    const int k2 = kt < KT ? kt * (GEMM_BK * 2) : DEAD;
+    uint4* as = ring + slot * STAGE;
+#pragma unroll
+    for (int j = 0; j < B_INS; ++j)
+      dma_slab(rb, as + BM * 8 + (wave * B_INS + j) * 64, vadd_sgpr(vb[j], k2));
+#pragma unroll
+    for (int j = 0; j < A_INS; ++j)
+      dma_slab(ra, as + (wave * A_INS + j) * 64, vadd_sgpr(va[j], k2));
+  };
+
+  // epilogue operands, requested ahead of the ring so that their latency is
+  // not exposed after it: a lane stores runs of 8 columns (8 lanes per row),
+  // the same columns in every run
+  constexpr int RUNS = 4 / WK;                        // runs per lane and 32-row slice
+  const int col = n0 + wn * 64 + (lane & 7) * 8;
+  const bool col_ok = col < N;
+  uint32_t bb[4] = {0u, 0u, 0u, 0u};
+  float gg[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  uint4 res[2][RUNS];
+  if constexpr (EPI != EPI_PARTIAL && EPI != EPI_BIAS_QKPOST) {
+    if (col_ok) {
+      const uint4 bw = *reinterpret_cast<const uint4*>(bias + col);
+      bb[0] = bw.x; bb[1] = bw.y; bb[2] = bw.z; bb[3] = bw.w;
+    }
+    if constexpr (EPI == EPI_BIAS_GATED_RESIDUAL) {
+      if (col_ok) {
+        const float4 g0 = *reinterpret_cast<const float4*>(gate + col);
+        const float4 g1 = *reinterpret_cast<const float4*>(gate + col + 4);
+        gg[0] = g0.x; gg[1] = g0.y; gg[2] = g0.z; gg[3] = g0.w;
+        gg[4] = g1.x; gg[5] = g1.y; gg[6] = g1.z; gg[7] = g1.w;
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int it = 0; it < RUNS; ++it) {
+          const int row = m0 + wm * 64 + i * 32 + (wk * RUNS + it) * 8 + (lane >> 3);
+          res[i][it] = (row < M && col_ok) ? *reinterpret_cast<const uint4*>(C + (int64_t)row * ldc + col)
+                                           : make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+  }
+
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+#pragma unroll
+  for (int p = 0; p < NST - 1; ++p) issue(p, kt0 + p);
+  const int khalf = lane >> 5, r31 = lane & 31, sw = lds_swz(r31);
+  int slot = 0, fill = NST - 1;
+  for (int kt = kt0; kt < KT; ++kt) {
+    // own loads of stage kt have landed and own reads of stage kt - 1 are done;
+    // after the barrier so are everyone's, which frees slot `fill` (stage kt - 1)
+    wait_stage<(NST - 2) * INS>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue(fill, kt + NST - 1);
+    const uint4* as = ring + slot * STAGE + wm * 64 * 8;
+    const uint4* bs = ring + slot * STAGE + (BM + wn * 64) * 8;
+#pragma unroll
+    for (int q = 0; q < 4 / WK; ++q) {
+      const int chunk = (2 * (wk * (4 / WK) + q) + khalf) ^ sw;
+      bf16x8 af[2], bf[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) af[i] = __builtin_bit_cast(bf16x8, as[(i * 32 + r31) * 8 + chunk]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) bf[j] = __builtin_bit_cast(bf16x8, bs[(j * 32 + r31) * 8 + chunk]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+    }
+    slot = slot + 1 == NST ? 0 : slot + 1;
+    fill = fill + 1 == NST ? 0 : fill + 1;
+  }
+  wait_stage<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  // epilogue: 32-row slices of the WK partial blocks through LDS, summed in
+  // block order
+  float* stage = reinterpret_cast<float*>(ring);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    float* own = stage + wave * 32 * EP_LD;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        own[(8 * (r >> 2) + 4 * khalf + (r & 3)) * EP_LD + j * 32 + r31] = acc[i][j][r];
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < RUNS; ++it) {
+      const int rl = (wk * RUNS + it) * 8 + (lane >> 3);
+      const int row = m0 + wm * 64 + i * 32 + rl;
+      float v[8];
+#pragma unroll
+      for (int p = 0; p < WK; ++p) {
+        const float* q = stage + (((wm * WN + wn) * WK + p) * 32 + rl) * EP_LD + (lane & 7) * 8;
+        const float4 a = reinterpret_cast<const float4*>(q)[0], b = reinterpret_cast<const float4*>(q)[1];
+        const float w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = p == 0 ? w[e] : v[e] + w[e];
+      }
+      if constexpr (EPI == EPI_BIAS_QKPOST) {
+        qkpost_store(v, bias, C, ldc, row, col, n0 + wn * 64, M, N, qp);
+      } else if (row < M && col_ok) {
+        if constexpr (EPI == EPI_PARTIAL) {
+          float* q = part + ((int64_t)z * M + row) * N + col;
+          reinterpret_cast<float4*>(q)[0] = make_float4(v[0], v[1], v[2], v[3]);
+          reinterpret_cast<float4*>(q)[1] = make_float4(v[4], v[5], v[6], v[7]);
+        } else {
+          bf16_t* dst = C + (int64_t)row * ldc + col;
+          uint32_t rr[4] = {0u, 0u, 0u, 0u};
+          if constexpr (EPI == EPI_BIAS_GATED_RESIDUAL) {
+            const uint4 rw = res[i][it];
+            rr[0] = rw.x; rr[1] = rw.y; rr[2] = rw.z; rr[3] = rw.w;
+            if (smap != nullptr) dst = Cs + (int64_t)smap[row] * ldc + col;
+          }
+          uint32_t out[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float b0 = __uint_as_float(bb[e] << 16), b1 = __uint_as_float(bb[e] & 0xFFFF0000u);
+            const float x0 = __uint_as_float(rr[e] << 16), x1 = __uint_as_float(rr[e] & 0xFFFF0000u);
+            out[e] = pack_bf16x2(epi_value<EPI>(v[2 * e], b0, gg[2 * e], x0),
+                                 epi_value<EPI>(v[2 * e + 1], b1, gg[2 * e + 1], x1));
+          }
+          *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
+        }
+      }
+    }
+    if (i == 0) __syncthreads();
+  }
+}
+
+template <int ROLE, int WM, int WN, int WK, int NST, int EPI>
+static hipError_t run_ring(const RingArgs& a, int splits, hipStream_t st) {
+  const int tiles_m = (a.M + 64 * WM - 1) / (64 * WM), tiles_n = (a.N + 64 * WN - 1) / (64 * WN);
+  hipLaunchKernelGGL((gemm_ring<ROLE, WM, WN, WK, NST, EPI>), dim3(tiles_m * tiles_n * splits),
+                     dim3(WM * WN * WK * 64), 0, st, (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B,
+                     a.ldb, (const bf16_t*)a.bias, a.gate, (bf16_t*)a.C, a.ldc, a.M, a.N, a.K,
+                     tiles_m, tiles_n, splits, a.part, a.qp, (bf16_t*)a.Cs, a.smap);
+  return hipGetLastError();
+}
+
+template <int ROLE, int EPI>
+static hipError_t run_ring_tile(int tile, const RingArgs& a, int splits, hipStream_t st) {
+  switch (tile) {
+    case RING_64x64: return run_ring<ROLE, 1, 1, 4, 4, EPI>(a, splits, st);
+    case RING_64x128: return run_ring<ROLE, 1, 2, 2, 3, EPI>(a, splits, st);
+    case RING_128x64: return run_ring<ROLE, 2, 1, 2, 3, EPI>(a, splits, st);
+    case RING_128x128: return run_ring<ROLE, 2, 2, 2, 3, EPI>(a, splits, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_ring(int role, const RingArgs& a, const RingPlan& p, hipStream_t st) {
+  const bool post = a.qp.qk_norm || a.qp.tab != nullptr;
+  switch (role) {
+    case ROLE_QKV:
+      if (p.splits > 1) return run_ring_tile<ROLE_QKV, EPI_PARTIAL>(p.tile, a, p.splits, st);
+      return post ? run_ring_tile<ROLE_QKV, EPI_BIAS_QKPOST>(p.tile, a, 1, st)
+                  : run_ring_tile<ROLE_QKV, EPI_BIAS>(p.tile, a, 1, st);
+    case ROLE_UP:
+      if (p.splits > 1) return run_ring_tile<ROLE_UP, EPI_PARTIAL>(p.tile, a, p.splits, st);
+      return run_ring_tile<ROLE_UP, EPI_BIAS_GELU>(p.tile, a, 1, st);
+    case ROLE_OUT:
+      if (p.splits > 1) return run_ring_tile<ROLE_OUT, EPI_PARTIAL>(p.tile, a, p.splits, st);
+      return run_ring_tile<ROLE_OUT, EPI_BIAS_GATED_RESIDUAL>(p.tile, a, 1, st);
+    case ROLE_DOWN:
+      if (p.splits > 1) return run_ring_tile<ROLE_DOWN, EPI_PARTIAL>(p.tile, a, p.splits, st);
+      return run_ring_tile<ROLE_DOWN, EPI_BIAS_GATED_RESIDUAL>(p.tile, a, 1, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace swam

@@ -38,11 +38,19 @@ enum GemmRole { ROLE_QKV = 0, ROLE_OUT = 1, ROLE_UP = 2, ROLE_DOWN = 3 };
 // ldc) instead of C[m]; the residual is still read from C[m].  The scatter of
 // a packed sequence's rows back into the full latent rides on the last
 // projection this way.
+// ln (OUT / DOWN without smap, ldc == N): where K is split, the pass that sums
+// the splits also computes h = LN(result) (1 + scale) + shift and sets `done`;
+// otherwise the caller launches that LayerNorm itself.
+struct LnNext {
+  void* h;
+  const float *shift, *scale;
+  bool done = false;
+};
 hipError_t launch_gemm(int dtype, int role, const void* A, int64_t lda, const void* B,
                        int64_t ldb, const void* bias, const float* gate, void* C,
                        int64_t ldc, int64_t M, int64_t N, int64_t K, hipStream_t st,
                        float* ws = nullptr, int64_t ws_floats = 0, void* Cs = nullptr,
-                       const int32_t* smap = nullptr);
+                       const int32_t* smap = nullptr, LnNext* ln = nullptr);
 
 // QKV projection C = A . B^T + bias followed by the QK-norm / rotary
 // embedding of qp on its q and k columns, with the same bf16 rounding of the
@@ -64,6 +72,12 @@ hipError_t launch_adaln(int dtype, const AdalnArgs& a, int n_blk, const float* t
 // h[r] = LN(x[r]) (1 + scale) + shift
 hipError_t launch_ln_mod(int dtype, const void* x, void* h, const float* shift,
                          const float* scale, int64_t rows, int d, hipStream_t st);
+// the LayerNorm behind a bf16 projection whose K was split: x[r] += gate *
+// (sum of the `splits` partial rows + bias), stored, and h[r] of that row;
+// part is [splits][rows][d]
+hipError_t launch_splitk_ln(const float* part, int splits, int64_t rows, int d, const void* bias,
+                            const float* gate, void* x, void* h, const float* shift,
+                            const float* scale, hipStream_t st);
 // the same on gathered rows: xp[r] = x_full[gather[r]] (the gather-pack) and
 // h[r] = LN(xp[r]) (1 + scale) + shift, in one pass
 hipError_t launch_ln_mod_gather(int dtype, const void* x_full, const int32_t* gather, void* xp,

@@ -313,10 +313,14 @@ bool bad_block(const swam_block_weights* w) {
 // scatter_to (bf16, last block of a sparse step): the MLP down projection
 // stores row r of its result into scatter_to at the cached gather position of
 // r (the scatter back into the full latent) instead of into x
+// next_mod (blocks of a step): the modulation of the block that follows.  Its
+// first LayerNorm may share the pass that sums this block's split down
+// projection; *h_ready says so to that block's call, which then skips it.
 int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* x,
               int64_t n_rows, const int32_t* cu, int n_seqs, float* lse_out, void* qkv,
               int pos_mode, const ScoreArgs* score = nullptr, const void* pack_src = nullptr,
-              void* pruned_dst = nullptr, bool score_in_up = false, void* scatter_to = nullptr) {
+              void* pruned_dst = nullptr, bool score_in_up = false, void* scatter_to = nullptr,
+              const float* next_mod = nullptr, bool* h_ready = nullptr) {
   const int dt = c->cfg.dtype;
   const int64_t d = c->dv.d, hid = c->dv.hidden;
   void* h = c->ptr<char>(c->lay.h);
@@ -336,7 +340,7 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
     }
     if (pruned_dst)
       if (int rc = fork_pruned_copy(c, pack_src, pruned_dst)) return rc;
-  } else {
+  } else if (!h_ready || !*h_ready) {
     Timed t(c, SWAM_T_LNMOD);
     SWAM_HIP(c, launch_ln_mod(dt, x, h, sh1, sc1, n_rows, (int)d, st), "ln_mod");
   }
@@ -381,12 +385,13 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
     SWAM_HIP(c, hipEventRecord(c->ev_score, c->side), "scoring done");
     c->score_pending = true;
   }
+  LnNext ln2{h, sh2, sc2};
   {
     Timed t(c, SWAM_T_GEMM_OUT);
     SWAM_HIP(c, launch_gemm(dt, ROLE_OUT, o, d, w->w_o, d, w->b_o, g1, x, d,
-                            n_rows, d, d, st, sk, sk_n), "gemm out");
+                            n_rows, d, d, st, sk, sk_n, nullptr, nullptr, &ln2), "gemm out");
   }
-  {
+  if (!ln2.done) {
     Timed t(c, SWAM_T_LNMOD);
     SWAM_HIP(c, launch_ln_mod(dt, x, h, sh2, sc2, n_rows, (int)d, st), "ln_mod 2");
   }
@@ -401,13 +406,16 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
     SWAM_HIP(c, launch_gemm(dt, ROLE_UP, h, d, w->w_1, d, w->b_1, nullptr, u, hid, n_rows,
                             hid, d, st, sk, sk_n), "gemm up");
   }
+  LnNext ln1{h, next_mod, next_mod ? next_mod + d : nullptr};
   {
     Timed t(c, SWAM_T_GEMM_DOWN);
     SWAM_HIP(c, launch_gemm(dt, ROLE_DOWN, u, hid, w->w_2, hid, w->b_2, g2, x, d,
                             n_rows, d, hid, st, sk, sk_n, scatter_to,
-                            scatter_to ? c->ptr<int32_t>(c->lay.gather) : nullptr),
+                            scatter_to ? c->ptr<int32_t>(c->lay.gather) : nullptr,
+                            next_mod && !scatter_to ? &ln1 : nullptr),
              scatter_to ? "gemm down + unpack" : "gemm down");
   }
+  if (h_ready) *h_ready = ln1.done;
   return SWAM_OK;
 }
 
@@ -1031,12 +1039,14 @@ int enqueue_step_launches(swam_ctx* c, const swam_model* model, const void* x_fu
     const bool in_up = score && cf.dtype == SWAM_BF16 &&
                        gemm_up_scored_slots(c->dv.rows_full, c->dv.hidden, d,
                                             c->dv.splitk_floats) > 0;
+    bool h_ready = false;
     for (int l = 0; l < cf.n_blocks; ++l) {
       a.s_out = c->ptr<float>(c->lay.s_all) + (int64_t)l * cf.n_frames * c->dv.n_s;
       rc = run_block(c, &model->blocks[l], mod + (int64_t)l * 6 * d, y_full, c->dv.rows_full,
                      c->ptr<int32_t>(c->lay.cu_dense), cf.batch,
                      score ? c->ptr<float>(c->lay.lse) : nullptr, qkv, 0,
-                     score ? &a : nullptr, nullptr, nullptr, in_up && l + 1 < cf.n_blocks);
+                     score ? &a : nullptr, nullptr, nullptr, in_up && l + 1 < cf.n_blocks, nullptr,
+                     l + 1 < cf.n_blocks ? mod + (int64_t)(l + 1) * 6 * d : nullptr, &h_ready);
       if (rc != SWAM_OK) return rc;
     }
     if (score) {
@@ -1066,12 +1076,14 @@ int enqueue_step_launches(swam_ctx* c, const swam_model* model, const void* x_fu
     // copy's, disjoint from these); fp32: a separate scatter pass
     void* xp = c->ptr<char>(c->lay.xp);
     const bool fold_unpack = cf.dtype == SWAM_BF16;
+    bool h_ready = false;
     for (int l = 0; l < cf.n_blocks; ++l) {
       const bool last = l + 1 == cf.n_blocks;
       rc = run_block(c, &model->blocks[l], mod + (int64_t)l * 6 * d, xp, c->packed_rows,
                      c->ptr<int32_t>(c->lay.cu_packed), cf.batch, nullptr, qkv, 1, nullptr,
                      l == 0 ? x_full : nullptr, l == 0 && fork ? y_full : nullptr, false,
-                     fold_unpack && last ? y_full : nullptr);
+                     fold_unpack && last ? y_full : nullptr,
+                     last ? nullptr : mod + (int64_t)(l + 1) * 6 * d, &h_ready);
       if (rc != SWAM_OK) return rc;
     }
     if (fork) SWAM_HIP(c, hipStreamWaitEvent(c->st, c->ev_score, 0), "join pruned-row copy");
