@@ -126,11 +126,11 @@ struct RingArgs {
   void* C; int64_t ldc;
   int M, N, K;
   float* part;                 // [splits][M][N] partial sums when splits > 1
-  QkPost qp;                   // QKV only
+  QkPost qp;                   // bf16 QKV only
   void* Cs; const int32_t* smap;
 };
 // one projection of role `role` (GemmRole); splits > 1 leaves the partial sums
 // in a.part and the epilogue to the caller
-hipError_t launch_ring(int role, const RingArgs& a, const RingPlan& p, hipStream_t st);
+hipError_t launch_ring(int dtype, int role, const RingArgs& a, const RingPlan& p, hipStream_t st);
 
 }  // namespace swam

@@ -12,7 +12,8 @@
 //   row-major V tile.  K and V tiles are DMA'd global -> LDS (no register
 //   staging), double-buffered.  Online softmax in the log2 domain with the
 //   1/8 scale folded into one FMA, tail-only masking and lazy rescaling.
-// fp32 path: one wave per (query row, head), online softmax with shuffles.
+// fp32 path: 32 query rows of one head per workgroup, its four waves taking
+// every fourth 32-key tile, both products on 32x32x2 fp32 MFMAs.
 #include "common.h"
 
 #include <type_traits>
@@ -263,34 +264,105 @@ attn_fwd_bf16(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* _
     lse[(int64_t)qrow * n_heads + h] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
 }
 
-// fp32: one wave per (query row, head); lane = head-dim element.
-__global__ void __launch_bounds__(64)
+// fp32: S^T = K Q^T and O^T = V^T P^T with 32x32x2 MFMAs in the operand roles
+// of the bf16 kernel (one query per lane; the P^T accumulators are the B
+// operand as they are, key pairs 4 apart).  K, Q and V fragments come straight
+// from global memory: an MFMA takes 64 cycles for 4 or 16 bytes per lane, so
+// the loads hide behind it and no tile is staged.  The four waves' partial
+// (max, sum, O) over their keys are merged through LDS in a fixed order.  The
+// key split keeps short sequences from running on a few CUs: 192 rows of 24
+// heads are 144 workgroups (one wave per row and head took 106 us there).
+__global__ void __launch_bounds__(256)
 attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ out, float* __restrict__ lse,
-             const int32_t* __restrict__ cu, int n_seqs, int n_heads, int64_t n_rows) {
-  const int64_t row = blockIdx.x;
-  const int h = blockIdx.y, lane = threadIdx.x;
-  if (row >= n_rows) return;
-  int s0 = 0, s1 = 0;
-  for (int b = 0; b < n_seqs; ++b) {
-    const int e = (int)min((int64_t)max(cu[b + 1], 0), n_rows);
-    const int a = min(max(cu[b], 0), e);
-    if (row >= a && row < e) { s0 = a; s1 = e; }
-  }
-  if (s1 <= s0) return;
+             const int32_t* __restrict__ cu, int n_seqs, int n_heads, int n_rows) {
+  constexpr int LD = 68;                         // fp32 pitch of a query's partial O row
+  __shared__ float os[4][32][LD];
+  __shared__ float ms[4][32], ls[4][32];
+  const int h = blockIdx.y;
+  int s0, s1, q0;
+  if (!find_tile<32>(cu, n_seqs, n_rows, blockIdx.x, s0, s1, q0)) return;
   const int d = n_heads * 64;
   const int64_t ld = 3 * (int64_t)d;
-  const float q = qkv[row * ld + h * 64 + lane] * 0.125f;
-  float m = -INFINITY, l = 0.0f, acc = 0.0f;
-  for (int j = s0; j < s1; ++j) {
-    const float x = warp_sum(q * qkv[(int64_t)j * ld + d + h * 64 + lane]);
-    const float mn = fmaxf(m, x);
-    const float corr = expf(m - mn), p = expf(x - mn);
-    l = l * corr + p;
-    acc = acc * corr + p * qkv[(int64_t)j * ld + 2 * d + h * 64 + lane];
-    m = mn;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, r31 = lane & 31;
+  const float* kbase = qkv + d + h * 64;
+  const float* vbase = qkv + 2 * d + h * 64 + r31;
+  f32x4 qf[8];
+  {
+    const float* qp = qkv + (int64_t)min(q0 + r31, s1 - 1) * ld + h * 64;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const f32x4*>(qp + 4 * (2 * s + g)) * 0.125f;
   }
-  out[row * d + h * 64 + lane] = acc / l;
-  if (lse != nullptr && lane == 0) lse[row * n_heads + h] = m + logf(l);
+  f32x16 o[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[t][r] = 0.0f;
+  float m = -INFINITY, l = 0.0f;
+  for (int kb = s0 + 32 * wave; kb < s1; kb += 128) {
+    const float* kp = kbase + (int64_t)min(kb + r31, s1 - 1) * ld;
+    f32x4 kf[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) kf[s] = *reinterpret_cast<const f32x4*>(kp + 4 * (2 * s + g));
+    float vf[2][16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float* vp = vbase + (int64_t)min(kb + 8 * (r >> 2) + 4 * g + (r & 3), s1 - 1) * ld;
+      vf[0][r] = vp[0];
+      vf[1][r] = vp[32];
+    }
+    f32x16 st;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st[r] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) st = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s][e], qf[s][e], st, 0, 0, 0);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (kb + 8 * (r >> 2) + 4 * g + (r & 3) >= s1) st[r] = -INFINITY;
+      mx = fmaxf(mx, st[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m, mx), corr = expf(m - m_new);
+    m = m_new;
+    l *= corr;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[t][r] *= corr;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float p = expf(st[r] - m_new);
+      l += p;
+      o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[0][r], p, o[0], 0, 0, 0);
+      o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[1][r], p, o[1], 0, 0, 0);
+    }
+  }
+  l += __shfl_xor(l, 32);
+  if (g == 0) { ms[wave][r31] = m; ls[wave][r31] = l; }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+      *reinterpret_cast<float4*>(&os[wave][r31][32 * t + 8 * q4 + 4 * g]) =
+          make_float4(o[t][4 * q4], o[t][4 * q4 + 1], o[t][4 * q4 + 2], o[t][4 * q4 + 3]);
+  __syncthreads();
+  const int q = tid >> 3, c = (tid & 7) * 8, row = q0 + q;
+  if (row >= s1) return;
+  const float mt = fmaxf(fmaxf(ms[0][q], ms[1][q]), fmaxf(ms[2][q], ms[3][q]));
+  float lt = 0.0f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float f = expf(ms[w][q] - mt);         // 0 for a wave without keys
+    lt = fmaf(ls[w][q], f, lt);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = fmaf(os[w][q][c + e], f, acc[e]);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] /= lt;
+  store8(out + (int64_t)row * d + h * 64 + c, acc);
+  if (lse != nullptr && (tid & 7) == 0) lse[(int64_t)row * n_heads + h] = mt + logf(lt);
 }
 
 hipError_t launch_attention(int dtype, const void* qkv, void* o, float* lse,
@@ -322,8 +394,8 @@ hipError_t launch_attention(int dtype, const void* qkv, void* o, float* lse,
       SWAM_ATT(4, 1, 1, slots4);
 #undef SWAM_ATT
   } else {
-    hipLaunchKernelGGL(attn_fwd_f32, dim3((unsigned)n_rows, n_heads), dim3(64), 0, st,
-                       (const float*)qkv, (float*)o, lse, cu_seqlens, n_seqs, n_heads, n_rows);
+    hipLaunchKernelGGL(attn_fwd_f32, dim3((unsigned)((n_rows + 31) / 32 + n_seqs), n_heads), dim3(256),
+                       0, st, (const float*)qkv, (float*)o, lse, cu_seqlens, n_seqs, n_heads, (int)n_rows);
   }
   return hipGetLastError();
 }

@@ -307,98 +307,35 @@ gemm_bf16_nt(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict
 }
 
 // Sum of the split-K partials and the epilogue: one thread per 8 columns of
-// a row (16-byte bias / residual loads and stores, 32-byte partial loads).
-template <int ROLE, int EPI>
+// a row (16-byte loads and stores).
+template <int ROLE, typename T, int EPI>
 __global__ void __launch_bounds__(256)
 splitk_epilogue(const float* __restrict__ part, int splits, int M, int N,
-                const bf16_t* __restrict__ bias, const float* __restrict__ gate, bf16_t* C,
-                int64_t ldc, bf16_t* Cs, const int32_t* __restrict__ smap) {
+                const T* __restrict__ bias, const float* __restrict__ gate, T* C,
+                int64_t ldc, T* Cs, const int32_t* __restrict__ smap) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int cpr = N / 8;
   if (id >= (int64_t)M * cpr) return;
   const int row = (int)(id / cpr), col = (int)(id % cpr) * 8;
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int z = 0; z < splits; ++z) {
-    const float* q = part + ((int64_t)z * M + row) * N + col;
-    const float4 a = reinterpret_cast<const float4*>(q)[0], b = reinterpret_cast<const float4*>(q)[1];
-    v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
-    v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
+    float q[8];
+    load8(part + ((int64_t)z * M + row) * N + col, q);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += q[e];
   }
-  const uint4 bw = *reinterpret_cast<const uint4*>(bias + col);
-  const uint32_t bb[4] = {bw.x, bw.y, bw.z, bw.w};
-  bf16_t* p = C + (int64_t)row * ldc + col;
-  uint32_t rr[4] = {0u, 0u, 0u, 0u};
-  float gg[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float bb[8], gg[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float rr[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  load8(bias + col, bb);
+  T* dst = C + (int64_t)row * ldc + col;
   if (EPI == EPI_BIAS_GATED_RESIDUAL) {
-    const uint4 rw = *reinterpret_cast<const uint4*>(p);
-    rr[0] = rw.x; rr[1] = rw.y; rr[2] = rw.z; rr[3] = rw.w;
-    const float4 g0 = *reinterpret_cast<const float4*>(gate + col);
-    const float4 g1 = *reinterpret_cast<const float4*>(gate + col + 4);
-    gg[0] = g0.x; gg[1] = g0.y; gg[2] = g0.z; gg[3] = g0.w;
-    gg[4] = g1.x; gg[5] = g1.y; gg[6] = g1.z; gg[7] = g1.w;
-  }
-  uint32_t out[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float b0 = __uint_as_float(bb[e] << 16), b1 = __uint_as_float(bb[e] & 0xFFFF0000u);
-    const float x0 = __uint_as_float(rr[e] << 16), x1 = __uint_as_float(rr[e] & 0xFFFF0000u);
-    out[e] = pack_bf16x2(epi_value<EPI>(v[2 * e], b0, gg[2 * e], x0),
-                         epi_value<EPI>(v[2 * e + 1], b1, gg[2 * e + 1], x1));
-  }
-  bf16_t* dst = p;
-  if (EPI == EPI_BIAS_GATED_RESIDUAL && smap != nullptr) dst = Cs + (int64_t)smap[row] * ldc + col;
-  *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
-}
-
-// ---------------------------------------------------------------------------
-// fp32 path (plain LDS-tiled FMA; used by the fp32 workload)
-// ---------------------------------------------------------------------------
-template <int EPI>
-__global__ void __launch_bounds__(256)
-gemm_f32_nt(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
-            const float* __restrict__ bias, const float* __restrict__ gate, float* C,
-            int64_t ldc, int M, int N, int K) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = threadIdx.x; i < 64 * 16; i += 256) {
-      const int r = i >> 4, kk = i & 15;
-      const int gm = m0 + r, gn = n0 + r, gk = k0 + kk;
-      As[kk][r] = (gm < M && gk < K) ? A[(int64_t)gm * lda + gk] : 0.0f;
-      Bs[kk][r] = (gn < N && gk < K) ? B[(int64_t)gn * ldb + gk] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+    load8(dst, rr);
+    load8(gate + col, gg);
+    if (smap != nullptr) dst = Cs + (int64_t)smap[row] * ldc + col;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty + 16 * i;
-    if (row >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx + 16 * j;
-      if (col >= N) continue;
-      float* p = C + (int64_t)row * ldc + col;
-      const float resid = (EPI == EPI_BIAS_GATED_RESIDUAL) ? *p : 0.0f;
-      const float gv = (EPI == EPI_BIAS_GATED_RESIDUAL) ? gate[col] : 0.0f;
-      *p = epi_value<EPI>(acc[i][j], bias[col], gv, resid);
-    }
-  }
+  for (int e = 0; e < 8; ++e) v[e] = epi_value<EPI>(v[e], bb[e], gg[e], rr[e]);
+  store8(dst, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -505,12 +442,15 @@ static GemmPlan choose_gemm(int64_t M, int64_t N, int64_t K, int64_t ws_floats,
 // 1,000 rows at d = 1536, down projections from about 3,000).
 constexpr int RING_BM[RING_TILES] = {64, 64, 128, 128};
 constexpr int RING_BN[RING_TILES] = {64, 128, 64, 128};
-static GemmPlan choose_ring(int64_t M, int64_t N, int64_t K, int64_t ws_floats, bool ln_follows,
-                            int max_splits) {
-  const double t0[RING_TILES] = {4.0, 4.8, 4.8, 1.5}, fill[RING_TILES] = {0.33, 0.17, 0.19, 3.5},
-               step[RING_TILES] = {0.215, 0.392, 0.392, 0.51};
+// fp32 has no other kernel; its steps are bound by the fp32 matrix rate.
+static GemmPlan choose_ring(int dtype, int64_t M, int64_t N, int64_t K, int64_t ws_floats,
+                            bool ln_follows, int max_splits) {
+  const double t0[RING_TILES] = {4.0, 4.8, 4.8, 1.5}, fill[RING_TILES] = {0.33, 0.17, 0.19, 3.5};
+  const double step16[RING_TILES] = {0.215, 0.392, 0.392, 0.51},
+               step32[RING_TILES] = {0.55, 1.05, 1.05, 2.1};
+  const double* step = dtype == 1 ? step16 : step32;
   const int split_opts[6] = {1, 2, 3, 4, 6, 8};
-  const int64_t kt = K / GEMM_BK;
+  const int64_t kt = K / (dtype == 1 ? GEMM_BK : GEMM_BK / 2);
   GemmPlan best{0, 1, true, 1e30};
   for (int i = 0; i < RING_TILES; ++i) {
     const int64_t tiles = ((M + RING_BM[i] - 1) / RING_BM[i]) * ((N + RING_BN[i] - 1) / RING_BN[i]);
@@ -530,18 +470,31 @@ static GemmPlan choose_ring(int64_t M, int64_t N, int64_t K, int64_t ws_floats, 
 // next (out and down projections)
 static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t ws_floats, bool ln_follows) {
   const GemmPlan c = choose_gemm(M, N, K, ws_floats);
-  const GemmPlan r = choose_ring(M, N, K, ws_floats, ln_follows, 8);
+  const GemmPlan r = choose_ring(1, M, N, K, ws_floats, ln_follows, 8);
   return r.us < c.us ? r : c;
 }
 
-template <int ROLE, int EPI>
+template <int ROLE, typename T, int EPI>
 static hipError_t run_epilogue(const float* ws, int splits, int M, int N, const void* bias,
                                const float* gate, void* C, int64_t ldc, void* Cs,
                                const int32_t* smap, hipStream_t st) {
   const int64_t n = (int64_t)M * (N / 8);
-  hipLaunchKernelGGL((splitk_epilogue<ROLE, EPI>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                     ws, splits, M, N, (const bf16_t*)bias, gate, (bf16_t*)C, ldc, (bf16_t*)Cs, smap);
+  hipLaunchKernelGGL((splitk_epilogue<ROLE, T, EPI>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                     ws, splits, M, N, (const T*)bias, gate, (T*)C, ldc, (T*)Cs, smap);
   return hipGetLastError();
+}
+
+// after a projection of `splits` K slices: the sum and epilogue, with the
+// LayerNorm that follows where the caller asks for it
+template <int ROLE, typename T, int EPI>
+static hipError_t finish_splits(const float* ws, int splits, int M, int N, const void* bias,
+                                const float* gate, void* C, int64_t ldc, void* Cs,
+                                const int32_t* smap, LnNext* ln, hipStream_t st) {
+  if (splits <= 1) return hipSuccess;
+  if (ln == nullptr || N > LN_ROW_MAX)
+    return run_epilogue<ROLE, T, EPI>(ws, splits, M, N, bias, gate, C, ldc, Cs, smap, st);
+  ln->done = true;
+  return launch_splitk_ln(sizeof(T) == 2, ws, splits, M, N, bias, gate, C, ln->h, ln->shift, ln->scale, st);
 }
 
 // ln (out and down projections): a LayerNorm of the result into ln->h follows;
@@ -556,7 +509,7 @@ static hipError_t dispatch_bf16(const void* A, int64_t lda, const void* B, int64
   hipError_t e;
   if (p.ring) {
     const RingArgs a{A, lda, B, ldb, bias, gate, C, ldc, M, N, K, ws, QkPost{}, Cs, smap};
-    e = launch_ring(ROLE, a, {p.tile, p.splits}, st);
+    e = launch_ring(1, ROLE, a, {p.tile, p.splits}, st);
   } else if (p.tile == 0) {
     e = run_bf16<ROLE, 256, 256, 2, 4, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
   } else if (p.tile == 2) {
@@ -567,11 +520,7 @@ static hipError_t dispatch_bf16(const void* A, int64_t lda, const void* B, int64
     e = run_bf16<ROLE, 128, 128, 2, 2, EPI>(A, lda, B, ldb, bias, gate, C, ldc, M, N, K, p.splits, ws, st, QkPost{}, Cs, smap);
   }
   if (e != hipSuccess) return e;
-  if (p.splits <= 1) return hipSuccess;
-  if (ln == nullptr)
-    return run_epilogue<ROLE, EPI>(ws, p.splits, M, N, bias, gate, C, ldc, Cs, smap, st);
-  ln->done = true;
-  return launch_splitk_ln(ws, p.splits, M, N, bias, gate, C, ln->h, ln->shift, ln->scale, st);
+  return finish_splits<ROLE, bf16_t, EPI>(ws, p.splits, M, N, bias, gate, C, ldc, Cs, smap, ln, st);
 }
 
 // The MLP up projection with one layer's scoring in the tail of its grid:
@@ -633,14 +582,15 @@ hipError_t launch_gemm_up_scored(const void* A, int64_t lda, const void* B, int6
   return run_up_scored<128, 128, 2, 2>(A, lda, B, ldb, bias, C, ldc, m, n, k, sa, n_sw, st);
 }
 
-template <int EPI>
+template <int ROLE, int EPI>
 static hipError_t run_f32(const void* A, int64_t lda, const void* B, int64_t ldb,
                           const void* bias, const float* gate, void* C, int64_t ldc, int M,
-                          int N, int K, hipStream_t st) {
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  hipLaunchKernelGGL(gemm_f32_nt<EPI>, grid, dim3(256), 0, st, (const float*)A, lda,
-                     (const float*)B, ldb, (const float*)bias, gate, (float*)C, ldc, M, N, K);
-  return hipGetLastError();
+                          int N, int K, float* ws, int64_t ws_floats, LnNext* ln, hipStream_t st) {
+  const GemmPlan p = choose_ring(0, M, N, K, ws ? ws_floats : 0, ln != nullptr, 8);
+  const RingArgs a{A, lda, B, ldb, bias, gate, C, ldc, M, N, K, ws, QkPost{}, nullptr, nullptr};
+  const hipError_t e = launch_ring(0, ROLE, a, {p.tile, p.splits}, st);
+  if (e != hipSuccess) return e;
+  return finish_splits<ROLE, float, EPI>(ws, p.splits, M, N, bias, gate, C, ldc, nullptr, nullptr, ln, st);
 }
 
 hipError_t launch_gemm(int dtype, int role, const void* A, int64_t lda, const void* B,
@@ -664,10 +614,10 @@ hipError_t launch_gemm(int dtype, int role, const void* A, int64_t lda, const vo
     }
   }
   switch (role) {
-    case ROLE_QKV: return run_f32<EPI_BIAS>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, st);
-    case ROLE_UP: return run_f32<EPI_BIAS_GELU>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, st);
-    case ROLE_OUT:
-    case ROLE_DOWN: return run_f32<EPI_BIAS_GATED_RESIDUAL>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, st);
+    case ROLE_QKV: return run_f32<ROLE_QKV, EPI_BIAS>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, nullptr, st);
+    case ROLE_UP: return run_f32<ROLE_UP, EPI_BIAS_GELU>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, nullptr, st);
+    case ROLE_OUT: return run_f32<ROLE_OUT, EPI_BIAS_GATED_RESIDUAL>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, ln, st);
+    case ROLE_DOWN: return run_f32<ROLE_DOWN, EPI_BIAS_GATED_RESIDUAL>(A, lda, B, ldb, bias, gate, C, ldc, m, n, k, ws, ws_floats, ln, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -681,10 +631,10 @@ hipError_t launch_gemm_qkv(int dtype, const void* A, int64_t lda, const void* B,
   if (dtype == 1 && post) {
     const GemmPlan p = choose_gemm(M, N, K, ws ? ws_floats : 0, true);
     const int m = (int)M, n = (int)N, k = (int)K;
-    const GemmPlan r = choose_ring(M, N, K, 0, false, 1);
+    const GemmPlan r = choose_ring(1, M, N, K, 0, false, 1);
     if (r.us < p.us) {
       const RingArgs a{A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, nullptr, qp, nullptr, nullptr};
-      return launch_ring(ROLE_QKV, a, {r.tile, 1}, st);
+      return launch_ring(1, ROLE_QKV, a, {r.tile, 1}, st);
     }
     if (p.splits <= 1) {
       if (p.tile == 0)

@@ -147,20 +147,26 @@ ln_mod_bf16(const bf16_t* __restrict__ x, bf16_t* __restrict__ h,
   }
 }
 
-// Sum of split-K partial rows, gated residual and the LayerNorm behind it: one
-// workgroup per row, thread t holding the 8-column chunks t, t + blockDim, ...
-// (up to CH), all partial loads of a chunk issued together.  Latency-bound at
-// the row counts that split K (a few hundred): one row per workgroup spreads
-// them over all CUs, and the pass replaces an epilogue pass and a LayerNorm
-// pass (192 x 1536, 6 slices: 4.9 us against 4.7 + 4.7).
-template <int CH>
+// One workgroup per row, thread t holding the 8-column chunks t, t + blockDim,
+// ... (up to CH) in registers between the passes:
+//   LN_PLAIN : h = LN(x) (1 + scale) + shift
+//   LN_GATHER: the same of x row gather[r], which is also stored to xp
+//   LN_SPLIT : x += gate (sum of the split-K partial rows + bias), stored, and
+//              h of that row (rounded to the storage type first)
+// Latency-bound at the row counts that use it (a few hundred): one row per
+// workgroup spreads them over all CUs.  LN_SPLIT replaces an epilogue pass and
+// a LayerNorm pass (192 x 1536, 6 slices: 4.9 us against 4.7 + 4.7); fp32 rows
+// took 18 us for 192 x 1536 with one wave re-reading its row in 4-byte loads.
+enum LnRowMode { LN_PLAIN, LN_GATHER, LN_SPLIT };
+template <typename T, int CH, int MODE>
 __global__ void __launch_bounds__(256)
-splitk_ln_bf16(const float* __restrict__ part, int splits, int64_t slice,
-               const bf16_t* __restrict__ bias, const float* __restrict__ gate,
-               bf16_t* __restrict__ x, bf16_t* __restrict__ h, const float* __restrict__ shift,
-               const float* __restrict__ scale, int d) {
+ln_row(const float* __restrict__ part, int splits, int64_t slice, const T* __restrict__ bias,
+       const float* __restrict__ gate, const T* x, T* xp, T* __restrict__ h,
+       const float* __restrict__ shift, const float* __restrict__ scale, int d,
+       const int32_t* __restrict__ gather) {
   __shared__ float red[2][4];
   const int64_t row = blockIdx.x;
+  const int64_t src = MODE == LN_GATHER ? (int64_t)gather[row] : row;
   const int nch = d >> 3, tid = threadIdx.x, wave = tid >> 6, nw = blockDim.x >> 6;
   float v[CH][8];
   float s = 0.0f;
@@ -169,34 +175,28 @@ splitk_ln_bf16(const float* __restrict__ part, int splits, int64_t slice,
     const int ci = tid + (int)blockDim.x * c;
     if (ci >= nch) continue;
     const int col = ci * 8;
-    const uint4 bw = *reinterpret_cast<const uint4*>(bias + col);
-    const uint4 xw = *reinterpret_cast<const uint4*>(x + row * d + col);
-    const float4 ga = *reinterpret_cast<const float4*>(gate + col);
-    const float4 gb = *reinterpret_cast<const float4*>(gate + col + 4);
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const float* p = part + row * d + col;
+    load8(x + src * d + col, v[c]);
+    if constexpr (MODE == LN_SPLIT) {
+      float bb[8], gg[8], acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      load8(bias + col, bb);
+      load8(gate + col, gg);
+      const float* p = part + row * d + col;
 #pragma unroll 4
-    for (int z = 0; z < splits; ++z) {
-      const float4 a = *reinterpret_cast<const float4*>(p + z * slice);
-      const float4 b = *reinterpret_cast<const float4*>(p + z * slice + 4);
-      acc[0] += a.x; acc[1] += a.y; acc[2] += a.z; acc[3] += a.w;
-      acc[4] += b.x; acc[5] += b.y; acc[6] += b.z; acc[7] += b.w;
-    }
-    const uint32_t bb[4] = {bw.x, bw.y, bw.z, bw.w}, xx[4] = {xw.x, xw.y, xw.z, xw.w};
-    const float gg[8] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z, gb.w};
-    uint32_t o[4];
+      for (int z = 0; z < splits; ++z) {
+        float q[8];
+        load8(p + z * slice, q);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float lo = __uint_as_float(xx[e] << 16) + gg[2 * e] * (acc[2 * e] + __uint_as_float(bb[e] << 16));
-      const float hi = __uint_as_float(xx[e] & 0xFFFF0000u) +
-                       gg[2 * e + 1] * (acc[2 * e + 1] + __uint_as_float(bb[e] & 0xFFFF0000u));
-      o[e] = pack_bf16x2(lo, hi);
-      // the LayerNorm reads the stored (rounded) row
-      v[c][2 * e] = __uint_as_float(o[e] << 16);
-      v[c][2 * e + 1] = __uint_as_float(o[e] & 0xFFFF0000u);
-      s += v[c][2 * e] + v[c][2 * e + 1];
+        for (int e = 0; e < 8; ++e) acc[e] += q[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[c][e] = v[c][e] + gg[e] * (acc[e] + bb[e]);
+        if constexpr (sizeof(T) == 2) v[c][e] = bf16_to_f32(f32_to_bf16(v[c][e]));
+      }
     }
-    *reinterpret_cast<uint4*>(x + row * d + col) = make_uint4(o[0], o[1], o[2], o[3]);
+    if constexpr (MODE != LN_PLAIN) store8(xp + row * d + col, v[c]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s += v[c][e];
   }
   auto block_sum = [&](float t, float* r) {
     t = warp_sum(t);
@@ -213,36 +213,48 @@ splitk_ln_bf16(const float* __restrict__ part, int splits, int64_t slice,
     if (tid + (int)blockDim.x * c < nch)
 #pragma unroll
       for (int e = 0; e < 8; ++e) { const float t = v[c][e] - mean; q += t * t; }
-  const float rstd = rsqrtf(block_sum(q, red[1]) / d + 1e-6f);
+  const float var = block_sum(q, red[1]) / d + 1e-6f;
+  const float rstd = sizeof(T) == 2 ? rsqrtf(var) : 1.0f / sqrtf(var);
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
     const int ci = tid + (int)blockDim.x * c;
     if (ci >= nch) continue;
     const int col = ci * 8;
-    uint32_t o[4];
+    float sc[8], sh[8];
+    load8(scale + col, sc);
+    load8(shift + col, sh);
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      o[e] = pack_bf16x2((v[c][2 * e] - mean) * rstd * (1.0f + scale[col + 2 * e]) + shift[col + 2 * e],
-                         (v[c][2 * e + 1] - mean) * rstd * (1.0f + scale[col + 2 * e + 1]) + shift[col + 2 * e + 1]);
-    *reinterpret_cast<uint4*>(h + row * d + col) = make_uint4(o[0], o[1], o[2], o[3]);
+    for (int e = 0; e < 8; ++e) v[c][e] = (v[c][e] - mean) * rstd * (1.0f + sc[e]) + sh[e];
+    store8(h + row * d + col, v[c]);
   }
 }
 
-hipError_t launch_splitk_ln(const float* part, int splits, int64_t rows, int d, const void* bias,
-                            const float* gate, void* x, void* h, const float* shift,
-                            const float* scale, hipStream_t st) {
-  if (rows <= 0) return hipSuccess;
+template <typename T, int MODE>
+static hipError_t run_ln_row(const float* part, int splits, int64_t rows, int d, const void* bias,
+                             const float* gate, const void* x, void* xp, void* h,
+                             const float* shift, const float* scale, const int32_t* gather,
+                             hipStream_t st) {
   const int nt = d <= 512 ? 64 : d <= 1024 ? 128 : d <= 1536 ? 192 : 256;
-#define SWAM_SLN(CH_)                                                                          \
-  hipLaunchKernelGGL(splitk_ln_bf16<CH_>, dim3((unsigned)rows), dim3(nt), 0, st, part, splits, \
-                     rows * d, (const bf16_t*)bias, gate, (bf16_t*)x, (bf16_t*)h, shift, scale, d)
-  if (d <= 2048) SWAM_SLN(1);
-  else SWAM_SLN(2);                                // d <= 4096 (bf16 limit)
-#undef SWAM_SLN
+#define SWAM_LNR(CH_)                                                                           \
+  hipLaunchKernelGGL((ln_row<T, CH_, MODE>), dim3((unsigned)rows), dim3(nt), 0, st, part,       \
+                     splits, rows * d, (const T*)bias, gate, (const T*)x, (T*)xp, (T*)h, shift, \
+                     scale, d, gather)
+  if (d <= 2048) SWAM_LNR(1);
+  else SWAM_LNR(2);                                // d <= LN_ROW_MAX
+#undef SWAM_LNR
   return hipGetLastError();
 }
 
-// fp32 rows: two passes over global memory (rows are L1/L2 resident);
+hipError_t launch_splitk_ln(int dtype, const float* part, int splits, int64_t rows, int d,
+                            const void* bias, const float* gate, void* x, void* h,
+                            const float* shift, const float* scale, hipStream_t st) {
+  if (rows <= 0) return hipSuccess;
+  if (d > LN_ROW_MAX) return hipErrorInvalidValue;
+  return dtype == 1 ? run_ln_row<bf16_t, LN_SPLIT>(part, splits, rows, d, bias, gate, x, x, h, shift, scale, nullptr, st)
+                    : run_ln_row<float, LN_SPLIT>(part, splits, rows, d, bias, gate, x, x, h, shift, scale, nullptr, st);
+}
+
+// fp32 rows wider than LN_ROW_MAX: two passes over global memory (rows are L1/L2 resident);
 // gather != NULL: as the bf16 GATHER variant
 __global__ void __launch_bounds__(256)
 ln_mod_f32(const float* __restrict__ x, float* __restrict__ h, const float* __restrict__ shift,
@@ -284,6 +296,9 @@ static hipError_t ln_mod_any(int dtype, const void* x, void* h, const float* shi
     else
       hipLaunchKernelGGL((ln_mod_bf16<8, GATHER>), grid, dim3(256), 0, st, xb, hb, shift, scale,
                          rows, d, gather, pb);
+  } else if (d <= LN_ROW_MAX) {
+    return run_ln_row<float, GATHER ? LN_GATHER : LN_PLAIN>(nullptr, 0, rows, d, nullptr, nullptr, x, xp,
+                                                            h, shift, scale, gather, st);
   } else {
     hipLaunchKernelGGL(ln_mod_f32, grid, dim3(256), 0, st, (const float*)x, (float*)h, shift,
                        scale, rows, d, GATHER ? gather : nullptr, (float*)xp);

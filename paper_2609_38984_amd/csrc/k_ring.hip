@@ -1,5 +1,5 @@
-// Projections of short token sets: C = epi(A . B^T + bias), M up to a few
-// thousand rows, bf16.
+// Projections of short token sets, C = epi(A . B^T + bias) with M up to a few
+// thousand rows (bf16), and every fp32 projection.
 //
 // What bounds these is not the matrix cores but the read of the weights (a
 // 192-row block of d = 1536 does 10.9 GFLOP on 57 MB of weights): a two-stage
@@ -14,6 +14,10 @@
 // different 16-column slices of each stage, so no operand fragment is read by
 // two waves of a block; their sums meet in LDS in a fixed order in the
 // epilogue.
+// fp32: the same ring, tiles and LDS layout with 16-byte chunks of four floats
+// (stages of 32 columns); a lane's chunk of A and of B feeds four 32x32x2 MFMAs,
+// one column pair (c, c + 4) each, so the sums stay fp32 products in fp32
+// accumulators.  Bound by the fp32 matrix rate (157 TFLOP/s nominal).
 // `splits` > 1: that many workgroups share a tile along K and store fp32
 // partial sums (EPI_PARTIAL) for splitk_epilogue or splitk_ln.
 #include "gemm_common.h"
@@ -38,12 +42,26 @@ __device__ __forceinline__ void dma_slab(__amdgpu_buffer_rsrc_t r, uint4* slab, 
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)slab, 16, off, 0, 0, 0);
 }
 
-template <int ROLE, int WM, int WN, int WK, int NST, int EPI>
+// acc += A B^T for one 16-byte chunk per lane of a 32-row A and B fragment.  The
+// fragments are values of the vector type: read through a pointer to the LDS
+// words the compiler waits for every DMA load in flight before each stage.
+__device__ __forceinline__ void mma_chunk(bf16x8 a, bf16x8 b, f32x16& acc) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma_chunk(f32x4 a, f32x4 b, f32x16& acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
+}
+template <typename T> struct Chunk { typedef f32x4 type; };
+template <> struct Chunk<bf16_t> { typedef bf16x8 type; };
+
+template <int ROLE, typename T, int WM, int WN, int WK, int NST, int EPI>
 __global__ void __launch_bounds__(WM * WN * WK * 64)
-gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ B, int64_t ldb,
-          const bf16_t* __restrict__ bias, const float* __restrict__ gate, bf16_t* C, int64_t ldc,
+gemm_ring(const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t ldb,
+          const T* __restrict__ bias, const float* __restrict__ gate, T* C, int64_t ldc,
           int M, int N, int K, int tiles_m, int tiles_n, int splits, float* __restrict__ part,
-          const QkPost qp, bf16_t* Cs, const int32_t* __restrict__ smap) {
+          const QkPost qp, T* Cs, const int32_t* __restrict__ smap) {
+  constexpr int EPC = 16 / (int)sizeof(T), BK = 8 * EPC;   // elements per chunk, columns per stage
   constexpr int NW = WM * WN * WK, BM = 64 * WM, BN = 64 * WN;
   constexpr int A_INS = BM / 8 / NW, B_INS = BN / 8 / NW, INS = A_INS + B_INS;
   static_assert(A_INS * 8 * NW == BM && B_INS * 8 * NW == BN, "tile/waves mismatch");
@@ -67,7 +85,7 @@ gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ 
   const int gsz = min(tiles_m - first_m, GROUP_M);
   const int tm = first_m + (t % in_group) % gsz, tn = (t % in_group) / gsz;
   const int m0 = tm * BM, n0 = tn * BN;
-  const int KT_all = K / GEMM_BK;
+  const int KT_all = K / BK;
   const int kt0 = KT_all * z / splits;
   const int KT = KT_all * (z + 1) / splits;
 
@@ -75,23 +93,23 @@ gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ 
   // as zeros, and so does every load of a stage past KT (offset DEAD)
   constexpr int DEAD = 0x40000000;
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(A + (int64_t)m0 * lda), (short)0, (int)(min(M - m0, BM) * lda * 2), SWAM_BUF_DWORD3);
+      (void*)(A + (int64_t)m0 * lda), (short)0, (int)(min(M - m0, BM) * lda * (int)sizeof(T)), SWAM_BUF_DWORD3);
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(B + (int64_t)n0 * ldb), (short)0, (int)(min(N - n0, BN) * ldb * 2), SWAM_BUF_DWORD3);
+      (void*)(B + (int64_t)n0 * ldb), (short)0, (int)(min(N - n0, BN) * ldb * (int)sizeof(T)), SWAM_BUF_DWORD3);
   const int lrow = lane >> 3;
   int va[A_INS], vb[B_INS];
 #pragma unroll
   for (int j = 0; j < A_INS; ++j) {
     const int r = (wave * A_INS + j) * 8 + lrow;
-    va[j] = (int)((r * lda + 8 * ((lane & 7) ^ lds_swz(r))) * 2);
+    va[j] = (int)(r * lda * (int)sizeof(T)) + 16 * ((lane & 7) ^ lds_swz(r));
   }
 #pragma unroll
   for (int j = 0; j < B_INS; ++j) {
     const int r = (wave * B_INS + j) * 8 + lrow;
-    vb[j] = (int)((r * ldb + 8 * ((lane & 7) ^ lds_swz(r))) * 2);
+    vb[j] = (int)(r * ldb * (int)sizeof(T)) + 16 * ((lane & 7) ^ lds_swz(r));
   }
   auto issue = [&](int slot, int kt) {
-    const int k2 = kt < KT ? kt * (GEMM_BK * 2) : DEAD;
+    const int k2 = kt < KT ? kt * 128 : DEAD;
     uint4* as = ring + slot * STAGE;
 #pragma unroll
     for (int j = 0; j < B_INS; ++j)
@@ -107,28 +125,24 @@ gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ 
   constexpr int RUNS = 4 / WK;                        // runs per lane and 32-row slice
   const int col = n0 + wn * 64 + (lane & 7) * 8;
   const bool col_ok = col < N;
-  uint32_t bb[4] = {0u, 0u, 0u, 0u};
   float gg[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  uint4 res[2][RUNS];
+  constexpr int VEC = (int)sizeof(T) / 2;             // 16-byte pieces of a run
+  uint4 bw[VEC], res[2][RUNS][VEC];                   // unconverted: nothing waits for them yet
   if constexpr (EPI != EPI_PARTIAL && EPI != EPI_BIAS_QKPOST) {
-    if (col_ok) {
-      const uint4 bw = *reinterpret_cast<const uint4*>(bias + col);
-      bb[0] = bw.x; bb[1] = bw.y; bb[2] = bw.z; bb[3] = bw.w;
-    }
+#pragma unroll
+    for (int p = 0; p < VEC; ++p)
+      bw[p] = col_ok ? reinterpret_cast<const uint4*>(bias + col)[p] : make_uint4(0u, 0u, 0u, 0u);
     if constexpr (EPI == EPI_BIAS_GATED_RESIDUAL) {
-      if (col_ok) {
-        const float4 g0 = *reinterpret_cast<const float4*>(gate + col);
-        const float4 g1 = *reinterpret_cast<const float4*>(gate + col + 4);
-        gg[0] = g0.x; gg[1] = g0.y; gg[2] = g0.z; gg[3] = g0.w;
-        gg[4] = g1.x; gg[5] = g1.y; gg[6] = g1.z; gg[7] = g1.w;
-      }
+      if (col_ok) load8(gate + col, gg);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int it = 0; it < RUNS; ++it) {
           const int row = m0 + wm * 64 + i * 32 + (wk * RUNS + it) * 8 + (lane >> 3);
-          res[i][it] = (row < M && col_ok) ? *reinterpret_cast<const uint4*>(C + (int64_t)row * ldc + col)
-                                           : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+          for (int p = 0; p < VEC; ++p)
+            res[i][it][p] = (row < M && col_ok) ? reinterpret_cast<const uint4*>(C + (int64_t)row * ldc + col)[p]
+                                                : make_uint4(0u, 0u, 0u, 0u);
         }
     }
   }
@@ -157,16 +171,17 @@ gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ 
 #pragma unroll
     for (int q = 0; q < 4 / WK; ++q) {
       const int chunk = (2 * (wk * (4 / WK) + q) + khalf) ^ sw;
-      bf16x8 af[2], bf[2];
+      typename Chunk<T>::type af[2], bf[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) af[i] = __builtin_bit_cast(bf16x8, as[(i * 32 + r31) * 8 + chunk]);
+      for (int i = 0; i < 2; ++i)
+        af[i] = __builtin_bit_cast(typename Chunk<T>::type, as[(i * 32 + r31) * 8 + chunk]);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) bf[j] = __builtin_bit_cast(bf16x8, bs[(j * 32 + r31) * 8 + chunk]);
+      for (int j = 0; j < 2; ++j)
+        bf[j] = __builtin_bit_cast(typename Chunk<T>::type, bs[(j * 32 + r31) * 8 + chunk]);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < 2; ++j) mma_chunk(af[i], bf[j], acc[i][j]);
     }
     slot = slot + 1 == NST ? 0 : slot + 1;
     fill = fill + 1 == NST ? 0 : fill + 1;
@@ -178,6 +193,8 @@ gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ 
   // epilogue: 32-row slices of the WK partial blocks through LDS, summed in
   // block order
   float* stage = reinterpret_cast<float*>(ring);
+  float bb[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if constexpr (EPI != EPI_PARTIAL && EPI != EPI_BIAS_QKPOST) load8(reinterpret_cast<const T*>(bw), bb);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     float* own = stage + wave * 32 * EP_LD;
@@ -201,6 +218,7 @@ gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ 
         for (int e = 0; e < 8; ++e) v[e] = p == 0 ? w[e] : v[e] + w[e];
       }
       if constexpr (EPI == EPI_BIAS_QKPOST) {
+        static_assert(sizeof(T) == 2, "the QK post-processing store is bf16");
         qkpost_store(v, bias, C, ldc, row, col, n0 + wn * 64, M, N, qp);
       } else if (row < M && col_ok) {
         if constexpr (EPI == EPI_PARTIAL) {
@@ -208,22 +226,15 @@ gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ 
           reinterpret_cast<float4*>(q)[0] = make_float4(v[0], v[1], v[2], v[3]);
           reinterpret_cast<float4*>(q)[1] = make_float4(v[4], v[5], v[6], v[7]);
         } else {
-          bf16_t* dst = C + (int64_t)row * ldc + col;
-          uint32_t rr[4] = {0u, 0u, 0u, 0u};
+          T* dst = C + (int64_t)row * ldc + col;
+          float rr[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
           if constexpr (EPI == EPI_BIAS_GATED_RESIDUAL) {
-            const uint4 rw = res[i][it];
-            rr[0] = rw.x; rr[1] = rw.y; rr[2] = rw.z; rr[3] = rw.w;
+            load8(reinterpret_cast<const T*>(res[i][it]), rr);
             if (smap != nullptr) dst = Cs + (int64_t)smap[row] * ldc + col;
           }
-          uint32_t out[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float b0 = __uint_as_float(bb[e] << 16), b1 = __uint_as_float(bb[e] & 0xFFFF0000u);
-            const float x0 = __uint_as_float(rr[e] << 16), x1 = __uint_as_float(rr[e] & 0xFFFF0000u);
-            out[e] = pack_bf16x2(epi_value<EPI>(v[2 * e], b0, gg[2 * e], x0),
-                                 epi_value<EPI>(v[2 * e + 1], b1, gg[2 * e + 1], x1));
-          }
-          *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
+          for (int e = 0; e < 8; ++e) v[e] = epi_value<EPI>(v[e], bb[e], gg[e], rr[e]);
+          store8(dst, v);
         }
       }
     }
@@ -231,45 +242,48 @@ gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ 
   }
 }
 
-template <int ROLE, int WM, int WN, int WK, int NST, int EPI>
+template <int ROLE, typename T, int WM, int WN, int WK, int NST, int EPI>
 static hipError_t run_ring(const RingArgs& a, int splits, hipStream_t st) {
   const int tiles_m = (a.M + 64 * WM - 1) / (64 * WM), tiles_n = (a.N + 64 * WN - 1) / (64 * WN);
-  hipLaunchKernelGGL((gemm_ring<ROLE, WM, WN, WK, NST, EPI>), dim3(tiles_m * tiles_n * splits),
-                     dim3(WM * WN * WK * 64), 0, st, (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B,
-                     a.ldb, (const bf16_t*)a.bias, a.gate, (bf16_t*)a.C, a.ldc, a.M, a.N, a.K,
-                     tiles_m, tiles_n, splits, a.part, a.qp, (bf16_t*)a.Cs, a.smap);
+  hipLaunchKernelGGL((gemm_ring<ROLE, T, WM, WN, WK, NST, EPI>), dim3(tiles_m * tiles_n * splits),
+                     dim3(WM * WN * WK * 64), 0, st, (const T*)a.A, a.lda, (const T*)a.B, a.ldb,
+                     (const T*)a.bias, a.gate, (T*)a.C, a.ldc, a.M, a.N, a.K, tiles_m, tiles_n,
+                     splits, a.part, a.qp, (T*)a.Cs, a.smap);
   return hipGetLastError();
 }
 
-template <int ROLE, int EPI>
-static hipError_t run_ring_tile(int tile, const RingArgs& a, int splits, hipStream_t st) {
-  switch (tile) {
-    case RING_64x64: return run_ring<ROLE, 1, 1, 4, 4, EPI>(a, splits, st);
-    case RING_64x128: return run_ring<ROLE, 1, 2, 2, 3, EPI>(a, splits, st);
-    case RING_128x64: return run_ring<ROLE, 2, 1, 2, 3, EPI>(a, splits, st);
-    case RING_128x128: return run_ring<ROLE, 2, 2, 2, 3, EPI>(a, splits, st);
+template <int ROLE, typename T, int EPI>
+static hipError_t run_ring_tile(const RingPlan& p, const RingArgs& a, hipStream_t st) {
+  switch (p.tile) {
+    case RING_64x64: return run_ring<ROLE, T, 1, 1, 4, 4, EPI>(a, p.splits, st);
+    case RING_64x128: return run_ring<ROLE, T, 1, 2, 2, 3, EPI>(a, p.splits, st);
+    case RING_128x64: return run_ring<ROLE, T, 2, 1, 2, 3, EPI>(a, p.splits, st);
+    case RING_128x128: return run_ring<ROLE, T, 2, 2, 2, 3, EPI>(a, p.splits, st);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_ring(int role, const RingArgs& a, const RingPlan& p, hipStream_t st) {
-  const bool post = a.qp.qk_norm || a.qp.tab != nullptr;
+template <int ROLE, typename T, int EPI>
+static hipError_t run_ring_role(const RingPlan& p, const RingArgs& a, hipStream_t st) {
+  if (p.splits > 1) return run_ring_tile<ROLE, T, EPI_PARTIAL>(p, a, st);
+  if constexpr (ROLE == ROLE_QKV && sizeof(T) == 2)
+    if (a.qp.qk_norm || a.qp.tab != nullptr) return run_ring_tile<ROLE, T, EPI_BIAS_QKPOST>(p, a, st);
+  return run_ring_tile<ROLE, T, EPI>(p, a, st);
+}
+
+template <typename T>
+static hipError_t launch_ring_t(int role, const RingArgs& a, const RingPlan& p, hipStream_t st) {
   switch (role) {
-    case ROLE_QKV:
-      if (p.splits > 1) return run_ring_tile<ROLE_QKV, EPI_PARTIAL>(p.tile, a, p.splits, st);
-      return post ? run_ring_tile<ROLE_QKV, EPI_BIAS_QKPOST>(p.tile, a, 1, st)
-                  : run_ring_tile<ROLE_QKV, EPI_BIAS>(p.tile, a, 1, st);
-    case ROLE_UP:
-      if (p.splits > 1) return run_ring_tile<ROLE_UP, EPI_PARTIAL>(p.tile, a, p.splits, st);
-      return run_ring_tile<ROLE_UP, EPI_BIAS_GELU>(p.tile, a, 1, st);
-    case ROLE_OUT:
-      if (p.splits > 1) return run_ring_tile<ROLE_OUT, EPI_PARTIAL>(p.tile, a, p.splits, st);
-      return run_ring_tile<ROLE_OUT, EPI_BIAS_GATED_RESIDUAL>(p.tile, a, 1, st);
-    case ROLE_DOWN:
-      if (p.splits > 1) return run_ring_tile<ROLE_DOWN, EPI_PARTIAL>(p.tile, a, p.splits, st);
-      return run_ring_tile<ROLE_DOWN, EPI_BIAS_GATED_RESIDUAL>(p.tile, a, 1, st);
+    case ROLE_QKV: return run_ring_role<ROLE_QKV, T, EPI_BIAS>(p, a, st);
+    case ROLE_UP: return run_ring_role<ROLE_UP, T, EPI_BIAS_GELU>(p, a, st);
+    case ROLE_OUT: return run_ring_role<ROLE_OUT, T, EPI_BIAS_GATED_RESIDUAL>(p, a, st);
+    case ROLE_DOWN: return run_ring_role<ROLE_DOWN, T, EPI_BIAS_GATED_RESIDUAL>(p, a, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_ring(int dtype, int role, const RingArgs& a, const RingPlan& p, hipStream_t st) {
+  return dtype == 1 ? launch_ring_t<bf16_t>(role, a, p, st) : launch_ring_t<float>(role, a, p, st);
 }
 
 }  // namespace swam

@@ -18,23 +18,6 @@
 
 namespace swam {
 
-// 8 consecutive elements of a T row as fp32 (one 16-byte load for bf16)
-template <typename T>
-__device__ __forceinline__ void load8(const T* p, float (&o)[8]) {
-  if constexpr (sizeof(T) == 2) {
-    const uint4 u = *reinterpret_cast<const uint4*>(p);
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      o[2 * e] = __uint_as_float(w[e] << 16);
-      o[2 * e + 1] = __uint_as_float(w[e] & 0xFFFF0000u);
-    }
-  } else {
-    const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
-    o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w; o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
-  }
-}
-
 // one thread per (latent row, 8 token columns): each output column reads its
 // W_in row (c contiguous values) in 16-byte pieces; 16-byte stores of x.
 // Needs c % 8 == 0 (the launcher falls back to scalar weight loads otherwise).

@@ -12,7 +12,7 @@
 // bf16: workgroup = 4 waves on 16 keys of one frame (score_unit.h); the MLP
 // up projection of a refresh step can run the same units in extra
 // workgroups of its own launch instead.
-// fp32: one thread per key.
+// fp32: one wave per key, lanes = 16 queries x 4 quarters of the head dim.
 // Mode B normaliser: lambda over all keys of the sequence, per (query, head),
 // as an online max/sum split over key chunks with wavefront-shuffle
 // reductions, combined in a second pass.
@@ -34,27 +34,36 @@ score_f32(const float* __restrict__ q, int64_t q_seq, int64_t q_row,
           int64_t s_seq, const float* __restrict__ alpha, int B, int F, int n_s, int H,
           int n_heads, int n_layers, int64_t q_lay, int64_t k_lay, int64_t lse_lay,
           int64_t s_lay) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  // one wave per key: lane (query slot a, quarter dg of the head dim)
+  const int64_t id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (id >= (int64_t)n_layers * B * F * n_s) return;
+  const int lane = threadIdx.x & 63, a = lane & 15, dg = lane >> 4;
   const int j = id % n_s, f = (id / n_s) % F, b = (id / ((int64_t)n_s * F)) % B;
   const int layer = (int)(id / ((int64_t)n_s * F * B));
   q += layer * q_lay;
   k += layer * k_lay;
   lse += layer * lse_lay;
   s_out += layer * s_lay;
-  const int g = H / F;
-  const float* kr = k + b * k_seq + (int64_t)(f * n_s + j) * k_row;
+  const int g = H / F, qa = f * g + min(a, g - 1);
+  const float aw = a < g ? alpha[a] : 0.0f;
+  const float* kr = k + b * k_seq + (int64_t)(f * n_s + j) * k_row + 16 * dg;
+  const float* qr = q + b * q_seq + (int64_t)qa * q_row + 16 * dg;
+  const float* lr = lse + (int64_t)b * lse_seq + (int64_t)qa * n_heads;
   float s = 0.0f;
   for (int h = 0; h < n_heads; ++h) {
-    for (int a = 0; a < g; ++a) {
-      const int qa = f * g + a;
-      const float* qr = q + b * q_seq + (int64_t)qa * q_row + h * 64;
-      float x = 0.0f;
-      for (int e = 0; e < 64; ++e) x = fmaf(qr[e], kr[h * 64 + e], x);
-      s += alpha[a] * expf(x * 0.125f - lse[(int64_t)b * lse_seq + (int64_t)qa * n_heads + h]);
-    }
+    float x = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x = fmaf(qr[h * 64 + e], kr[h * 64 + e], x);
+    x += __shfl_xor(x, 16);
+    x += __shfl_xor(x, 32);
+    s += aw * expf(x * 0.125f - lr[h]);
   }
-  s_out[(int64_t)b * s_seq + (int64_t)f * n_s + j] = s / (float)n_heads;
+  // sum over the query slots (the four quarters hold the same sums)
+  s += __shfl_xor(s, 8);
+  s += __shfl_xor(s, 4);
+  s += __shfl_xor(s, 2);
+  s += __shfl_xor(s, 1);
+  if (lane == 0) s_out[(int64_t)b * s_seq + (int64_t)f * n_s + j] = s / (float)n_heads;
 }
 
 // ---------------------------------------------------------------------------
@@ -124,7 +133,7 @@ hipError_t launch_score(int dtype, const ScoreArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(score_bf16, dim3(nl * a.B * a.F * ktiles), dim3(256), 0, st, a);
   } else {
     const int64_t n = (int64_t)nl * a.B * a.F * a.n_s;
-    hipLaunchKernelGGL(score_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+    hipLaunchKernelGGL(score_f32, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st,
                        (const float*)a.q, a.q_seq, a.q_row, (const float*)a.k, a.k_seq,
                        a.k_row, a.lse, a.lse_seq, a.s_out, a.s_seq, a.alpha, a.B, a.F, a.n_s,
                        a.H, a.n_heads, nl, a.q_lay, a.k_lay, a.lse_lay, a.s_lay);

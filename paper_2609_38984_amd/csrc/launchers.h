@@ -72,12 +72,14 @@ hipError_t launch_adaln(int dtype, const AdalnArgs& a, int n_blk, const float* t
 // h[r] = LN(x[r]) (1 + scale) + shift
 hipError_t launch_ln_mod(int dtype, const void* x, void* h, const float* shift,
                          const float* scale, int64_t rows, int d, hipStream_t st);
-// the LayerNorm behind a bf16 projection whose K was split: x[r] += gate *
+// widest row that one workgroup's registers hold (the ln_row kernels)
+constexpr int LN_ROW_MAX = 4096;
+// the LayerNorm behind a projection whose K was split: x[r] += gate *
 // (sum of the `splits` partial rows + bias), stored, and h[r] of that row;
-// part is [splits][rows][d]
-hipError_t launch_splitk_ln(const float* part, int splits, int64_t rows, int d, const void* bias,
-                            const float* gate, void* x, void* h, const float* shift,
-                            const float* scale, hipStream_t st);
+// part is [splits][rows][d], d <= LN_ROW_MAX
+hipError_t launch_splitk_ln(int dtype, const float* part, int splits, int64_t rows, int d,
+                            const void* bias, const float* gate, void* x, void* h,
+                            const float* shift, const float* scale, hipStream_t st);
 // the same on gathered rows: xp[r] = x_full[gather[r]] (the gather-pack) and
 // h[r] = LN(xp[r]) (1 + scale) + shift, in one pass
 hipError_t launch_ln_mod_gather(int dtype, const void* x_full, const int32_t* gather, void* xp,

@@ -27,7 +27,7 @@ thread_local std::string g_err;
 struct Derived {
   int64_t n_s, g, l_full, rows_full, k_max, k_eff, d, hidden, esz, t_pack_fixed;
   int64_t n_scored;   // sequences that are scored and selected (the conditional half with pairs)
-  int64_t splitk_floats;  // fp32 workspace of the split-K GEMM path (bf16 only)
+  int64_t splitk_floats;  // fp32 workspace of the split-K projections
   int mass_num, mass_den;
 };
 
@@ -108,9 +108,8 @@ int derive(const swam_config* c, Derived* dv, std::string* err) {
   dv->n_s = n_s;
   dv->n_scored = c->cfg_pairs ? c->batch / 2 : c->batch;
   // split-K partial sums: up to 8 slices of the widest projection, at most 128 MB
-  dv->splitk_floats = c->dtype == SWAM_BF16
-      ? std::min<int64_t>(8 * rows * std::max<int64_t>(3 * d, (int64_t)c->mlp_ratio * d), 32ll << 20)
-      : 0;
+  dv->splitk_floats =
+      std::min<int64_t>(8 * rows * std::max<int64_t>(3 * d, (int64_t)c->mlp_ratio * d), 32ll << 20);
   dv->g = g;
   dv->l_full = l_full;
   dv->rows_full = rows;
