@@ -12,7 +12,8 @@
 // which walks the pool in that order, sorts the keys in LDS with a bitonic
 // network and counts with exact integer codes floor(V 2^40) and a uint64
 // prefix scan.
-// Packing is an exclusive prefix sum of keep flags in original token order;
+// Packing is an exclusive prefix sum of keep flags in original token order (fixed
+// budgets: offsets known without a scan);
 // pack is a coalesced 16-byte row gather, unpack the matching scatter.
 #include "launchers.h"
 
@@ -101,15 +102,32 @@ __device__ __forceinline__ int next_pow2(int n) {
 }
 
 // ---------------------------------------------------------------------------
-// block-wide top-k by radix select (blockDim.x == SEL_THREADS)
+// block-wide top-k by radix select (any whole number of waves)
 // ---------------------------------------------------------------------------
-constexpr int SEL_EPT = SWAM_SEL_MAXNP / SEL_THREADS;   // positions per thread
+constexpr int SEL_EPT = 4;                               // positions per thread
+static_assert(SEL_EPT * SEL_THREADS >= SWAM_MAX_NS_DEV, "one workgroup covers a frame");
 
 struct SelScratch {
-  uint32_t hist[256];
-  int ws[SEL_THREADS / 64 + 1];
-  int pick[2];
+  uint32_t hist[4][256];
+  int ws[SEL_THREADS / 64];
 };
+
+// inclusive-to-exclusive scan over the workgroup with one barrier; ws must not
+// be in use by an earlier scan that a barrier has not separated
+__device__ __forceinline__ int block_rank(int v, int* ws) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) ws[wave] = x;
+  __syncthreads();
+  int base = 0;
+  for (int w = 0; w < wave; ++w) base += ws[w];
+  return base + x - v;
+}
 
 // Thread t owns positions [t * SEL_EPT, (t + 1) * SEL_EPT).  Among the
 // candidate positions, sel[] marks the k that come first in the order (ok
@@ -118,67 +136,70 @@ struct SelScratch {
 // (ok << 32 | j) and taking the first k.  Four passes of 8-bit digit
 // histograms (LDS atomics) narrow down the ok value of the k-th key; its
 // ties are then taken lowest position first by an exclusive scan in
-// position order.
+// position order.  Latency-bound, so the barriers are few: every pass has its
+// own histogram, cleared up front, and every wave scans it for itself (six
+// barriers in all; with one histogram, a scanning wave and a broadcast there
+// were 22, and the pool of 1,200 positions took 11.5 us).
 __device__ void block_topk(const uint32_t (&ok)[SEL_EPT], const bool (&cand)[SEL_EPT], int k,
                            bool (&sel)[SEL_EPT], SelScratch& sc) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int mine = 0;
-#pragma unroll
-  for (int e = 0; e < SEL_EPT; ++e) mine += cand[e];
-  int total;
-  block_excl_scan(mine, sc.ws, &total);
-  if (k >= total || k <= 0) {
-#pragma unroll
-    for (int e = 0; e < SEL_EPT; ++e) sel[e] = k > 0 && cand[e];
-    return;
-  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid; i < 4 * 256; i += blockDim.x) (&sc.hist[0][0])[i] = 0;
+  __syncthreads();
   uint32_t prefix = 0, pmask = 0;
   int need = k;                                 // keys still to take at or after `prefix`
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    for (int i = tid; i < 256; i += blockDim.x) sc.hist[i] = 0;
-    __syncthreads();
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int shift = 24 - 8 * p;
 #pragma unroll
     for (int e = 0; e < SEL_EPT; ++e)
-      if (cand[e] && (ok[e] & pmask) == prefix) atomicAdd(&sc.hist[(ok[e] >> shift) & 255u], 1u);
+      if (cand[e] && (ok[e] & pmask) == prefix) atomicAdd(&sc.hist[p][(ok[e] >> shift) & 255u], 1u);
     __syncthreads();
-    if (wave == 0) {
-      // the digit bucket that holds the need-th key: scan of the 256 counts
-      uint32_t c[4], s = 0;
+    // the digit bucket that holds the need-th key: scan of the 256 counts
+    uint32_t c[4], s = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) { c[q] = sc.hist[4 * lane + q]; s += c[q]; }
-      uint32_t x = s;
+    for (int q = 0; q < 4; ++q) { c[q] = sc.hist[p][4 * lane + q]; s += c[q]; }
+    uint32_t x = s;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-      }
-      const uint32_t before = x - s;
-      if (before < (uint32_t)need && (uint32_t)need <= x) {
-        uint32_t run = before;
-        int q = 0;
-        while (run + c[q] < (uint32_t)need) run += c[q++];
-        sc.pick[0] = 4 * lane + q;
-        sc.pick[1] = (int)run;
-      }
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o);
+      if (lane >= o) x += y;
     }
-    __syncthreads();
-    prefix |= (uint32_t)sc.pick[0] << shift;
+    if (p == 0 && (need <= 0 || (uint32_t)need >= (uint32_t)__shfl((int)x, 63))) {
+      // nothing, or every candidate (the same decision in every wave)
+#pragma unroll
+      for (int e = 0; e < SEL_EPT; ++e) sel[e] = need > 0 && cand[e];
+      __syncthreads();                          // the histograms are free again
+      return;
+    }
+    const uint32_t before = x - s;
+    const bool hit = before < (uint32_t)need && (uint32_t)need <= x;
+    uint32_t run = before, digit = 4 * lane;
+    if (hit)
+      for (int q = 0; q < 3 && run + c[q] < (uint32_t)need; ++q) { run += c[q]; ++digit; }
+    const int src = __ffsll((unsigned long long)__ballot(hit)) - 1;
+    digit = (uint32_t)__shfl((int)digit, src);
+    run = (uint32_t)__shfl((int)run, src);
+    prefix |= digit << shift;
     pmask |= 255u << shift;
-    need -= sc.pick[1];
-    __syncthreads();                            // pick is rewritten by the next pass
+    need -= (int)run;
   }
   // prefix is now the k-th key's ok value; take `need` of its ties
   int t = 0;
 #pragma unroll
   for (int e = 0; e < SEL_EPT; ++e) t += cand[e] && ok[e] == prefix;
-  int tt;
-  int rank = block_excl_scan(t, sc.ws, &tt);
+  int rank = block_rank(t, sc.ws);
 #pragma unroll
   for (int e = 0; e < SEL_EPT; ++e) {
     const bool tie = cand[e] && ok[e] == prefix;
     sel[e] = cand[e] && (ok[e] < prefix || (tie && rank < need));
     rank += tie;
   }
+}
+
+// threads of a workgroup that covers n_s positions
+static int sel_threads(int n_s) {
+  const int nt = (n_s + SEL_EPT - 1) / SEL_EPT;
+  return nt <= 256 ? 256 : nt <= 512 ? 512 : SEL_THREADS;
 }
 
 // ---------------------------------------------------------------------------
@@ -214,105 +235,100 @@ reduce_frames(const float* __restrict__ s_all, int n_s, double* __restrict__ fsu
   }
 }
 
-// one block (64 threads) per b: Q_l, core layers, weight sums
-__global__ void __launch_bounds__(64)
-reduce_layers(const double* __restrict__ fsum, const double* __restrict__ fent, int L, int F,
-              int n_s, int k_eff, float* __restrict__ q_out, double* __restrict__ qd,
-              int32_t* __restrict__ core, double* __restrict__ dens) {
+// Layer qualities, core layers, V and A: one workgroup per (b, 64 positions),
+// one wave per frame (waves take frames w, w + nw, ...).  Every workgroup forms
+// the L qualities of its sequence from the frame sums (a few hundred float64)
+// instead of waiting for a launch that does; V_all of its positions meets in
+// LDS for the mean and deviation over frames.  All sums are float64 in layer
+// (frame) order, rounded once.  28 layers of 8 x 1,200: 10.9 us, against
+// 5.8 + 6.2 + 3.9 us and two launch gaps for layers, positions and anchors apart.
+__global__ void __launch_bounds__(1024)
+reduce_maps(const float* __restrict__ s_all, const double* __restrict__ fsum,
+            const double* __restrict__ fent, int L, int F, int n_s, int k_eff, float cv,
+            float* __restrict__ q_out, int32_t* __restrict__ core, float* __restrict__ v_out,
+            float* __restrict__ a_out) {
+  __shared__ double qv[64], wc[64];
   __shared__ float q32[64];
-  __shared__ double qv[64];
   __shared__ int flag[64];
-  const int b = blockIdx.x, l = threadIdx.x;
-  if (l < L) {
+  __shared__ double dens[2];
+  __shared__ double vall[64][64];                // [frame][position]
+  const int b = blockIdx.y, tid = threadIdx.x;
+  if (tid < L) {
     double tot = 0.0, ent = 0.0;
+    const double* fs = fsum + ((int64_t)b * L + tid) * F;
+    const double* fe = fent + ((int64_t)b * L + tid) * F;
+#pragma unroll 8
     for (int f = 0; f < F; ++f) {
-      tot += fsum[((int64_t)b * L + l) * F + f];
-      ent += fent[((int64_t)b * L + l) * F + f];
+      tot += fs[f];
+      ent += fe[f];
     }
     const double R = tot / F;
     const double E = ent / (F * log((double)n_s));
     const double Q = R * (1.0 - E);
-    qv[l] = Q;
-    q32[l] = (float)Q;
-    qd[b * L + l] = Q;
-    q_out[b * L + l] = (float)Q;
+    qv[tid] = Q;
+    q32[tid] = (float)Q;
   }
   __syncthreads();
-  if (l < L) {
+  if (tid < L) {
     int rank = 0;
     for (int m = 0; m < L; ++m)
-      rank += (q32[m] > q32[l]) || (q32[m] == q32[l] && m < l);
-    flag[l] = rank < k_eff;
+      rank += (q32[m] > q32[tid]) || (q32[m] == q32[tid] && m < tid);
+    flag[tid] = rank < k_eff;
   }
   __syncthreads();
-  if (l == 0) {
+  if (tid == 0) {
     int n = 0;
     double dc = 0.0, da = 0.0;
     for (int m = 0; m < L; ++m) {
-      if (flag[m]) { core[b * k_eff + n++] = m; dc += qv[m]; }
+      if (flag[m]) {
+        if (blockIdx.x == 0) core[b * k_eff + n] = m;
+        ++n;
+        dc += qv[m];
+      }
       da += qv[m];
     }
-    dens[2 * b] = dc;
-    dens[2 * b + 1] = da;
+    dens[0] = dc;
+    dens[1] = da;
   }
-}
-
-// one thread per (b, f, j): V over the core layers and V_all over all layers
-// (float64 sums in layer order; V stored as float32, V_all kept in float64)
-__global__ void __launch_bounds__(256)
-reduce_positions(const float* __restrict__ s_all, const double* __restrict__ qd,
-                 const int32_t* __restrict__ core, const double* __restrict__ dens, int L,
-                 int F, int n_s, int k_eff, float* __restrict__ v_out,
-                 double* __restrict__ vall) {
-  const int bf = blockIdx.y;                 // b * F + f
-  const int b = bf / F, f = bf - b * F;
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n_s) return;
-  const double dc = dens[2 * b], da = dens[2 * b + 1];
-  const float* sb = s_all + (int64_t)b * L * F * n_s + (int64_t)f * n_s + j;
-  const int64_t ls = (int64_t)F * n_s;       // layer stride
-  const double* q = qd + (int64_t)b * L;
-  const int32_t* cl = core + b * k_eff;
-  double acc = 0.0;
-  if (dc != 0.0) {
-    for (int c = 0; c < k_eff; ++c) {
-      const int l = cl[c];
-      acc += q[l] * (double)sb[l * ls];
+  if (blockIdx.x == 0 && tid < L) q_out[b * L + tid] = q32[tid];
+  __syncthreads();
+  const double dc = dens[0], da = dens[1];
+  // a zero weight sum falls back to the unweighted mean
+  if (tid < L) {
+    wc[tid] = dc != 0.0 ? qv[tid] : 1.0;
+    if (da == 0.0) qv[tid] = 1.0;
+  }
+  __syncthreads();
+  const int lane = tid & 63, nw = blockDim.x >> 6;
+  const int j = blockIdx.x * 64 + lane;
+  const int64_t ls = (int64_t)F * n_s;           // layer stride
+  for (int f = tid >> 6; f < F; f += nw) {
+    const float* sb = s_all + (int64_t)b * L * ls + (int64_t)f * n_s + min(j, n_s - 1);
+    double acc = 0.0, all = 0.0;
+#pragma unroll 8
+    for (int l = 0; l < L; ++l) {
+      const double sv = (double)sb[l * ls];
+      if (flag[l]) acc += wc[l] * sv;
+      all += qv[l] * sv;
     }
-    acc /= dc;
-  } else {
-    for (int c = 0; c < k_eff; ++c) acc += (double)sb[cl[c] * ls];
-    acc /= k_eff;
+    acc /= dc != 0.0 ? dc : (double)k_eff;
+    all /= da != 0.0 ? da : (double)L;
+    if (j < n_s) v_out[((int64_t)b * F + f) * n_s + j] = (float)acc;
+    vall[f][lane] = all;
   }
-  v_out[(int64_t)bf * n_s + j] = (float)acc;
-  double all = 0.0;
-  if (da != 0.0) {
-    for (int l = 0; l < L; ++l) all += q[l] * (double)sb[l * ls];
-    all /= da;
-  } else {
-    for (int l = 0; l < L; ++l) all += (double)sb[l * ls];
-    all /= L;
+  __syncthreads();
+  if (tid < 64 && j < n_s) {
+    double mu = 0.0;
+    for (int f = 0; f < F; ++f) mu += vall[f][lane];
+    mu /= F;
+    double var = 0.0;
+    for (int f = 0; f < F; ++f) {
+      const double dv = vall[f][lane] - mu;
+      var += dv * dv;
+    }
+    const double sd = sqrt(var / F);
+    a_out[(int64_t)b * n_s + j] = mu != 0.0 ? (float)(mu / (1.0 + (double)cv * (sd / mu))) : 0.0f;
   }
-  vall[(int64_t)bf * n_s + j] = all;
-}
-
-// one thread per (b, j): mean and population std of V_all over frames, anchor key
-__global__ void __launch_bounds__(256)
-reduce_anchor(const double* __restrict__ vall, int F, int n_s, float cv, float* __restrict__ a_out) {
-  const int b = blockIdx.y;
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n_s) return;
-  const double* vb = vall + (int64_t)b * F * n_s + j;
-  double mu = 0.0;
-  for (int f = 0; f < F; ++f) mu += vb[(int64_t)f * n_s];
-  mu /= F;
-  double var = 0.0;
-  for (int f = 0; f < F; ++f) {
-    const double dv = vb[(int64_t)f * n_s] - mu;
-    var += dv * dv;
-  }
-  const double sd = sqrt(var / F);
-  a_out[(int64_t)b * n_s + j] = mu != 0.0 ? (float)(mu / (1.0 + (double)cv * (sd / mu))) : 0.0f;
 }
 
 // Overlap(P, Q) = sum_i min(P_i / sum P, Q_i / sum Q) per map (App. C
@@ -363,24 +379,17 @@ hipError_t launch_score_reduce(const ReduceArgs& a, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int k_eff = a.k_layer < a.L ? a.k_layer : a.L;
-  double* dens = a.frame_sum + (int64_t)a.B * a.L * a.F;   // 2B doubles after the frame sums
-  hipLaunchKernelGGL(reduce_layers, dim3(a.B), dim3(64), 0, st, a.frame_sum, a.frame_ent, a.L,
-                     a.F, a.n_s, k_eff, a.q, a.qd, a.core, dens);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(reduce_positions, dim3((a.n_s + 255) / 256, a.B * a.F), dim3(256), 0, st,
-                     a.s_all, a.qd, a.core, dens, a.L, a.F, a.n_s, k_eff, a.v, a.vall);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(reduce_anchor, dim3((a.n_s + 255) / 256, a.B), dim3(256), 0, st, a.vall,
-                     a.F, a.n_s, a.cv_penalty, a.a);
+  const int nw = a.F < 16 ? a.F : 16;
+  hipLaunchKernelGGL(reduce_maps, dim3((a.n_s + 63) / 64, a.B), dim3(64 * nw), 0, st, a.s_all,
+                     a.frame_sum, a.frame_ent, a.L, a.F, a.n_s, k_eff, a.cv_penalty, a.q, a.core,
+                     a.v, a.a);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // selection
 // ---------------------------------------------------------------------------
-// pool: top (N_s - K_s) of max_f V(f, j); one block per b
+// pool: top (N_s - K_s) of max_f V(f, j); one block per b (mass threshold)
 __global__ void __launch_bounds__(SEL_THREADS)
 select_pool(const float* __restrict__ v, int F, int n_s, int k_anchor,
             uint8_t* __restrict__ pool) {
@@ -420,39 +429,137 @@ __device__ __forceinline__ uint64_t mass_code(float x) {
   return man >> (-sh);
 }
 
-// cores: per (b, f), top K_c (or the mass-threshold count) of V(f, .) in P
+// fixed budgets: cores of one frame per workgroup, the top K_c of V(f, .) in P;
+// the pool (the same in every frame of a sequence) is formed by each of them:
+// 8 x 1,200 positions take 13.0 us, against 11.3 + 8.2 us and a launch gap apart
+__global__ void __launch_bounds__(SEL_THREADS)
+select_core_fixed(const float* __restrict__ v, int F, int n_s, int k_core, int k_anchor,
+                  uint8_t* __restrict__ core) {
+  __shared__ SelScratch sc;
+  const int bf = blockIdx.x, b = bf / F, own = bf - b * F;
+  const float* vb = v + (int64_t)b * F * n_s;
+  const int j0 = threadIdx.x * SEL_EPT;
+  float m[SEL_EPT], mine[SEL_EPT];
+  uint32_t ok[SEL_EPT];
+  bool cand[SEL_EPT], pool[SEL_EPT], sel[SEL_EPT];
+#pragma unroll
+  for (int e = 0; e < SEL_EPT; ++e) {
+    const int j = min(j0 + e, n_s - 1);
+    m[e] = vb[j];
+    mine[e] = vb[(int64_t)own * n_s + j];
+  }
+#pragma unroll 4
+  for (int f = 1; f < F; ++f)
+#pragma unroll
+    for (int e = 0; e < SEL_EPT; ++e) m[e] = fmaxf(m[e], vb[(int64_t)f * n_s + min(j0 + e, n_s - 1)]);
+#pragma unroll
+  for (int e = 0; e < SEL_EPT; ++e) {
+    cand[e] = j0 + e < n_s;
+    ok[e] = ~float_order(m[e]);
+  }
+  block_topk(ok, cand, n_s - k_anchor, pool, sc);
+  __syncthreads();                               // the scratch is free again
+#pragma unroll
+  for (int e = 0; e < SEL_EPT; ++e) ok[e] = ~float_order(mine[e]);
+  block_topk(ok, pool, k_core, sel, sc);
+#pragma unroll
+  for (int e = 0; e < SEL_EPT; ++e)
+    if (j0 + e < n_s) core[(int64_t)bf * n_s + j0 + e] = sel[e];
+}
+
+// fixed budgets: anchors, retained list and pack map of one frame per
+// workgroup.  The anchors (the same in every frame) are formed by each of them.
+// Every sequence keeps t_pack rows, so a frame's packed rows start at a known
+// offset and no scan over rows is needed; frame 0's workgroup writes the
+// context and action rows and the sequence offsets (8.9 us at 8 x 1,200 and
+// 10,160 rows; one workgroup for the anchors and lists and one for the map took
+// 15.1 + 10.0 us).  pair > 0: sequence
+// b + pair keeps the same positions (the partner of a guidance pair).
+__global__ void __launch_bounds__(SEL_THREADS)
+select_pack_fixed(const float* __restrict__ a, const uint8_t* __restrict__ core, int F, int n_s,
+                  int k_core, int k_anchor, int k_max, int n_ctx, int n_act, int64_t l_full,
+                  int pair, int batch, int32_t* __restrict__ keep_idx,
+                  int32_t* __restrict__ keep_cnt, int32_t* __restrict__ pack_pos,
+                  int32_t* __restrict__ gather, int32_t* __restrict__ cu) {
+  __shared__ SelScratch sc;
+  const int bf = blockIdx.x, b = bf / F, f = bf - b * F, tid = threadIdx.x;
+  const uint8_t* cb = core + (int64_t)b * F * n_s;
+  const int j0 = tid * SEL_EPT;
+  uint32_t ok[SEL_EPT];
+  bool cand[SEL_EPT], sel[SEL_EPT], kept[SEL_EPT];
+#pragma unroll
+  for (int e = 0; e < SEL_EPT; ++e) {
+    const int j = min(j0 + e, n_s - 1);
+    kept[e] = cb[(int64_t)f * n_s + j] != 0;
+    ok[e] = ~float_order(a[(int64_t)b * n_s + j]);
+  }
+  // positions no frame's core took
+  uint32_t used[SEL_EPT] = {0u, 0u, 0u, 0u};
+#pragma unroll 4
+  for (int g = 0; g < F; ++g)
+#pragma unroll
+    for (int e = 0; e < SEL_EPT; ++e) used[e] |= cb[(int64_t)g * n_s + min(j0 + e, n_s - 1)];
+#pragma unroll
+  for (int e = 0; e < SEL_EPT; ++e) cand[e] = j0 + e < n_s && used[e] == 0;
+  block_topk(ok, cand, k_anchor, sel, sc);
+  __syncthreads();
+  int n = 0;
+#pragma unroll
+  for (int e = 0; e < SEL_EPT; ++e) {
+    kept[e] = j0 + e < n_s && (kept[e] || sel[e]);
+    n += kept[e];
+  }
+  const int k_ret = k_core + k_anchor;
+  const int64_t t_pack = n_ctx + (int64_t)F * k_ret + n_act;
+  const int rank0 = block_rank(n, sc.ws);
+  for (int p = 0; p < (pair > 0 ? 2 : 1); ++p) {
+    const int64_t bb = b + p * (int64_t)pair;
+    const int64_t row0 = bb * l_full + n_ctx + (int64_t)f * n_s;          // full row of position 0
+    const int64_t pk0 = bb * t_pack + n_ctx + (int64_t)f * k_ret;         // packed row of rank 0
+    int32_t* out = keep_idx + (bb * F + f) * k_max;
+    int r = rank0;
+#pragma unroll
+    for (int e = 0; e < SEL_EPT; ++e) {
+      const int j = j0 + e;
+      if (j >= n_s) continue;
+      if (kept[e]) {
+        out[r] = j;
+        pack_pos[row0 + j] = (int32_t)(pk0 + r);
+        gather[pk0 + r] = (int32_t)(row0 + j);
+        ++r;
+      } else {
+        pack_pos[row0 + j] = -1;
+      }
+    }
+    for (int q = k_ret + tid; q < k_max; q += blockDim.x) out[q] = -1;
+    if (tid == 0) keep_cnt[bb * F + f] = k_ret;
+    if (f == 0) {
+      for (int t = tid; t < n_ctx + n_act; t += blockDim.x) {
+        const int64_t row = bb * l_full + (t < n_ctx ? t : l_full - n_act + (t - n_ctx));
+        const int64_t pk = bb * t_pack + (t < n_ctx ? t : t_pack - n_act + (t - n_ctx));
+        pack_pos[row] = (int32_t)pk;
+        gather[pk] = (int32_t)row;
+      }
+      if (tid == 0) cu[bb] = (int32_t)(bb * t_pack);
+    }
+  }
+  if (bf == 0 && tid == 0) cu[batch] = (int32_t)(batch * t_pack);
+}
+
+// mass-threshold cores of one frame per workgroup
 __global__ void __launch_bounds__(SEL_THREADS)
 select_core(const float* __restrict__ v, const uint8_t* __restrict__ pool, int F, int n_s,
-            int k_core, int k_anchor, int mass_num, int mass_den, uint8_t* __restrict__ core,
+            int k_anchor, int mass_num, int mass_den, uint8_t* __restrict__ core,
             int32_t* __restrict__ kcount) {
   __shared__ uint64_t keys[SWAM_SEL_MAXNP];
   __shared__ uint64_t ws64[SEL_THREADS / 64 + 1];
   __shared__ int fails;
-  __shared__ SelScratch sc;
   const int bf = blockIdx.x;               // b * F + f
   const int b = bf / F;
   const int np = next_pow2(n_s);
   const float* vr = v + (int64_t)bf * n_s;
   const uint8_t* pb = pool + (int64_t)b * n_s;
   uint8_t* cr = core + (int64_t)bf * n_s;
-  if (mass_den == 0) {
-    // fixed budget: the top K_c of the pool by radix select
-    uint32_t ok[SEL_EPT];
-    bool cand[SEL_EPT], sel[SEL_EPT];
-    const int j0 = threadIdx.x * SEL_EPT;
-#pragma unroll
-    for (int e = 0; e < SEL_EPT; ++e) {
-      const int j = j0 + e;
-      cand[e] = j < n_s && pb[j];
-      ok[e] = cand[e] ? ~float_order(vr[j]) : ~0u;
-    }
-    block_topk(ok, cand, k_core, sel, sc);
-#pragma unroll
-    for (int e = 0; e < SEL_EPT; ++e)
-      if (j0 + e < n_s) cr[j0 + e] = sel[e];
-    if (threadIdx.x == 0) kcount[bf] = min(k_core, n_s - k_anchor);
-    return;
-  }
   // mass threshold: the pool in TopK order (full sort), walked with the codes
   for (int j = threadIdx.x; j < np; j += blockDim.x) {
     uint64_t key = ~0ull;
@@ -466,35 +573,32 @@ select_core(const float* __restrict__ v, const uint8_t* __restrict__ pool, int F
   __syncthreads();
   bitonic_sort(keys, np);
   const int psize = n_s - k_anchor;
-  int kc = k_core;
-  if (mass_den > 0) {
-    // T = sum of codes over every position of the frame
-    uint64_t part = 0;
-    for (int j = threadIdx.x; j < n_s; j += blockDim.x) part += mass_code(vr[j]);
-    uint64_t T;
-    block_excl_scan_u64(part, ws64, &T);
-    // inclusive prefix of codes in ranked order; each thread owns a contiguous run
-    const int ept = (psize + blockDim.x - 1) / blockDim.x;
-    const int r0 = threadIdx.x * ept;
-    uint64_t local = 0;
-    for (int r = r0; r < min(r0 + ept, psize); ++r)
-      local += mass_code(vr[(int)(keys[r] & 0xFFFFFFFFu)]);
-    uint64_t tot;
-    uint64_t run = block_excl_scan_u64(local, ws64, &tot);
-    int nf = 0;
-    for (int r = r0; r < min(r0 + ept, psize); ++r) {
-      run += mass_code(vr[(int)(keys[r] & 0xFFFFFFFFu)]);
-      nf += ((uint64_t)mass_den * run < (uint64_t)mass_num * T);
-    }
-    if (nf) atomicAdd(&fails, nf);
-    __syncthreads();
-    kc = min(1 + fails, psize);
+  // T = sum of codes over every position of the frame
+  uint64_t part = 0;
+  for (int j = threadIdx.x; j < n_s; j += blockDim.x) part += mass_code(vr[j]);
+  uint64_t T;
+  block_excl_scan_u64(part, ws64, &T);
+  // inclusive prefix of codes in ranked order; each thread owns a contiguous run
+  const int ept = (psize + blockDim.x - 1) / blockDim.x;
+  const int r0 = threadIdx.x * ept;
+  uint64_t local = 0;
+  for (int r = r0; r < min(r0 + ept, psize); ++r)
+    local += mass_code(vr[(int)(keys[r] & 0xFFFFFFFFu)]);
+  uint64_t tot;
+  uint64_t run = block_excl_scan_u64(local, ws64, &tot);
+  int nf = 0;
+  for (int r = r0; r < min(r0 + ept, psize); ++r) {
+    run += mass_code(vr[(int)(keys[r] & 0xFFFFFFFFu)]);
+    nf += ((uint64_t)mass_den * run < (uint64_t)mass_num * T);
   }
+  if (nf) atomicAdd(&fails, nf);
+  __syncthreads();
+  const int kc = min(1 + fails, psize);
   for (int r = threadIdx.x; r < kc; r += blockDim.x) cr[(int)(keys[r] & 0xFFFFFFFFu)] = 1;
   if (threadIdx.x == 0) kcount[bf] = kc;
 }
 
-// anchors + retained sets + keep flags; one block per b
+// mass threshold: anchors + retained sets + keep flags; one block per b
 __global__ void __launch_bounds__(SEL_THREADS)
 select_anchor(const float* __restrict__ a, const uint8_t* __restrict__ core, int F, int n_s,
               int k_anchor, int k_max, int n_ctx, int n_act, int64_t l_full,
@@ -550,18 +654,41 @@ select_anchor(const float* __restrict__ a, const uint8_t* __restrict__ core, int
 
 hipError_t launch_select(const SelectArgs& s, hipStream_t st) {
   const int64_t l_full = s.n_ctx + (int64_t)s.F * s.n_s + s.n_act;
+  hipError_t e;
+  if (s.mass_den == 0) {
+    const int nt = sel_threads(s.n_s);
+    hipLaunchKernelGGL(select_core_fixed, dim3(s.B * s.F), dim3(nt), 0, st, s.v, s.F, s.n_s, s.k_core,
+                       s.k_anchor, s.core);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(select_pack_fixed, dim3(s.B * s.F), dim3(nt), 0, st, s.a, s.core, s.F, s.n_s,
+                       s.k_core, s.k_anchor, s.k_max, s.n_ctx, s.n_act, l_full, s.batch - s.B,
+                       s.batch, s.keep_idx, s.keep_cnt, s.pack_pos, s.gather, s.cu);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(select_pool, dim3(s.B), dim3(SEL_THREADS), 0, st, s.v, s.F, s.n_s,
                      s.k_anchor, s.pool);
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(select_core, dim3(s.B * s.F), dim3(SEL_THREADS), 0, st, s.v, s.pool, s.F,
-                     s.n_s, s.k_core, s.k_anchor, s.mass_num, s.mass_den, s.core, s.keep_cnt);
+                     s.n_s, s.k_anchor, s.mass_num, s.mass_den, s.core, s.keep_cnt);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(select_anchor, dim3(s.B), dim3(SEL_THREADS), 0, st, s.a, s.core, s.F,
                      s.n_s, s.k_anchor, s.k_max, s.n_ctx, s.n_act, l_full, s.keep_idx,
                      s.keep_cnt, s.keep);
-  return hipGetLastError();
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (s.batch > s.B) {
+    // the unconditional partner b + B keeps the positions selected for b
+    const int64_t n[3] = {s.B * l_full, (int64_t)s.B * s.F * s.k_max, (int64_t)s.B * s.F};
+    int32_t* p[3] = {s.keep, s.keep_idx, s.keep_cnt};
+    CopyList c{};
+    for (int i = 0; i < 3; ++i) c.add(p[i], p[i] + n[i], n[i] * 4);
+    e = launch_copy_list(c, st);
+    if (e != hipSuccess) return e;
+  }
+  return launch_packmap(s.keep, s.pack_pos, s.gather, s.cu, s.batch, l_full, st);
 }
 
 // imported selection -> keep flags, normalised keep_idx / keep_cnt (ascending, deduplicated)
@@ -750,6 +877,32 @@ __global__ void __launch_bounds__(256)
 copy_chunks(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
     dst[i] = src[i];
+}
+
+// several buffers copied by one launch (blockIdx.y = buffer): 16-byte pieces
+// where both ends allow, else words
+__global__ void __launch_bounds__(256) copy_list(const CopyList c) {
+  const int i = blockIdx.y;
+  const int64_t words = c.bytes[i] / 4, step = (int64_t)gridDim.x * 256;
+  const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const uint32_t* s = (const uint32_t*)c.src[i];
+  uint32_t* d = (uint32_t*)c.dst[i];
+  int64_t done = 0;
+  if ((((uintptr_t)s | (uintptr_t)d) & 15) == 0) {
+    const int64_t n = words / 4;
+    for (int64_t t = t0; t < n; t += step) reinterpret_cast<uint4*>(d)[t] = reinterpret_cast<const uint4*>(s)[t];
+    done = n * 4;
+  }
+  for (int64_t t = done + t0; t < words; t += step) d[t] = s[t];
+}
+
+hipError_t launch_copy_list(const CopyList& c, hipStream_t st) {
+  if (c.n == 0) return hipSuccess;
+  int64_t most = 0;
+  for (int i = 0; i < c.n; ++i) most = c.bytes[i] > most ? c.bytes[i] : most;
+  const int64_t g = (most / 16 + 255) / 256;
+  hipLaunchKernelGGL(copy_list, dim3((unsigned)(g < 1 ? 1 : g > 1024 ? 1024 : g), c.n), dim3(256), 0, st, c);
+  return hipGetLastError();
 }
 
 static unsigned grid_for(int64_t chunks) {

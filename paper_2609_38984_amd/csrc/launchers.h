@@ -134,25 +134,42 @@ struct ReduceArgs {
   double* frame_ent;   // ws [B][L][F]
   float* q;            // [B][L]
   int32_t* core;       // [B][k_layer_eff]
-  double* qd;          // ws [B][L] float64 quality
   float* v;            // [B][F][N_s]
   float* a;            // [B][N_s]
-  double* vall;        // ws [B][F][N_s] float64 V_all
   int B, L, F, n_s, k_layer;
   float cv_penalty;
 };
 hipError_t launch_score_reduce(const ReduceArgs& a, hipStream_t st);
 
-// Selection and packing metadata.
+// buffers copied by one launch (word-aligned, whole words)
+struct CopyList {
+  static constexpr int MAX = 9;
+  const void* src[MAX];
+  void* dst[MAX];
+  int64_t bytes[MAX];
+  int n;
+  void add(const void* s, void* d, int64_t b) {
+    if (b <= 0) return;
+    src[n] = s; dst[n] = d; bytes[n] = b; ++n;
+  }
+};
+hipError_t launch_copy_list(const CopyList& c, hipStream_t st);
+
+// Selection and packing metadata (pack_pos, gather, cu) of fixed budgets or a
+// mass threshold.
 struct SelectArgs {
   const float* v;      // [B][F][N_s]
   const float* a;      // [B][N_s]
-  uint8_t* pool;       // ws [B][N_s]
+  uint8_t* pool;       // ws [B][N_s] (mass threshold)
   uint8_t* core;       // ws [B][F][N_s]
-  int32_t* keep_idx;   // [B][F][k_max]
-  int32_t* keep_cnt;   // [B][F]
-  int32_t* keep;       // ws [B*L_full] 0/1
+  int32_t* keep_idx;   // [batch][F][k_max]
+  int32_t* keep_cnt;   // [batch][F]
+  int32_t* keep;       // ws [batch*L_full] 0/1 (mass threshold)
+  int32_t* pack_pos;   // [batch*L_full]
+  int32_t* gather;     // [batch*L_full]
+  int32_t* cu;         // [batch+1]
   int B, F, n_s, k_core, k_anchor, k_max;
+  int batch;               // B, or 2 B: sequence b + B keeps the positions of b
   int mass_num, mass_den;  // mass threshold as a fraction; den == 0: fixed K_c
   int n_ctx, n_act;
 };

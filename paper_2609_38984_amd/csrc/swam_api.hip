@@ -33,7 +33,7 @@ struct Derived {
 
 // workspace layout (offsets into one arena)
 struct Layout {
-  size_t qkv, h, o, u, xp, lse, mod, alpha, rope, splitk, lse_act, lse_part, s_all, q, qd, core, v, a, vall,
+  size_t qkv, h, o, u, xp, lse, mod, alpha, rope, splitk, lse_act, lse_part, s_all, q, core, v, a,
       fsum, fent, pool, corefl, keep_idx, keep_cnt, keep, pack_pos, gather, cu_packed, cu_dense, total;
 };
 
@@ -158,12 +158,10 @@ Layout layout_for(const swam_config* c, const Derived& dv) {
   L.lse_part = take(B * chunks * c->n_act * c->n_heads * 2 * 4);
   L.s_all = take(B * Lb * F * dv.n_s * 4);
   L.q = take(B * Lb * 4);
-  L.qd = take(B * Lb * 8);
   L.core = take(B * dv.k_eff * 4);
   L.v = take(B * F * dv.n_s * 4);
   L.a = take(B * dv.n_s * 4);
-  L.vall = take(B * F * dv.n_s * 8);
-  L.fsum = take((B * Lb * F + 2 * B) * 8);
+  L.fsum = take(B * Lb * F * 8);
   L.fent = take(B * Lb * F * 8);
   L.pool = take(B * dv.n_s);
   L.corefl = take(B * F * dv.n_s);
@@ -440,10 +438,8 @@ int run_reduce(swam_ctx* c, const float* s_all, hipStream_t on = nullptr) {
   r.frame_ent = c->ptr<double>(c->lay.fent);
   r.q = c->ptr<float>(c->lay.q);
   r.core = c->ptr<int32_t>(c->lay.core);
-  r.qd = c->ptr<double>(c->lay.qd);
   r.v = c->ptr<float>(c->lay.v);
   r.a = c->ptr<float>(c->lay.a);
-  r.vall = c->ptr<double>(c->lay.vall);
   r.B = (int)c->dv.n_scored;
   r.L = cf.n_blocks;
   r.F = cf.n_frames;
@@ -479,7 +475,11 @@ int run_select(swam_ctx* c, const float* v, const float* a, int k_core = -1, int
   s.keep_idx = c->ptr<int32_t>(c->lay.keep_idx);
   s.keep_cnt = c->ptr<int32_t>(c->lay.keep_cnt);
   s.keep = c->ptr<int32_t>(c->lay.keep);
+  s.pack_pos = c->ptr<int32_t>(c->lay.pack_pos);
+  s.gather = c->ptr<int32_t>(c->lay.gather);
+  s.cu = c->ptr<int32_t>(c->lay.cu_packed);
   s.B = (int)c->dv.n_scored;
+  s.batch = cf.batch;
   s.F = cf.n_frames;
   s.n_s = (int)c->dv.n_s;
   s.k_core = k_core >= 0 ? k_core : cf.k_core;
@@ -492,21 +492,6 @@ int run_select(swam_ctx* c, const float* v, const float* a, int k_core = -1, int
   {
     Timed t(c, SWAM_T_SELECT, st);
     SWAM_HIP(c, launch_select(s, st), "select");
-    if (cf.cfg_pairs) {
-      // the unconditional partner b + B/2 keeps the positions selected for b
-      const int64_t P = c->dv.n_scored;
-      const size_t kb = (size_t)(P * c->dv.l_full) * 4, ib = (size_t)(P * cf.n_frames * c->dv.k_max) * 4,
-                   cb = (size_t)(P * cf.n_frames) * 4;
-      SWAM_HIP(c, hipMemcpyAsync((char*)s.keep + kb, s.keep, kb, hipMemcpyDeviceToDevice, st),
-               "share keep");
-      SWAM_HIP(c, hipMemcpyAsync((char*)s.keep_idx + ib, s.keep_idx, ib, hipMemcpyDeviceToDevice,
-                                 st), "share keep_idx");
-      SWAM_HIP(c, hipMemcpyAsync((char*)s.keep_cnt + cb, s.keep_cnt, cb, hipMemcpyDeviceToDevice,
-                                 st), "share keep_cnt");
-    }
-    SWAM_HIP(c, launch_packmap(s.keep, c->ptr<int32_t>(c->lay.pack_pos),
-                               c->ptr<int32_t>(c->lay.gather), c->ptr<int32_t>(c->lay.cu_packed),
-                               cf.batch, c->dv.l_full, st), "packmap");
   }
   if (c->dv.mass_den > 0) {
     const int rc = read_packed_rows(c, st);
@@ -518,12 +503,15 @@ int run_select(swam_ctx* c, const float* v, const float* a, int k_core = -1, int
   return SWAM_OK;
 }
 
-int copy_out(swam_ctx* c, void* dst, size_t src_off, size_t bytes, const char* what) {
-  if (!dst) return SWAM_OK;
-  SWAM_HIP(c, hipMemcpyAsync(dst, c->arena + src_off, bytes, hipMemcpyDeviceToDevice, c->st),
-           what);
-  return SWAM_OK;
-}
+// the requested pieces of the workspace (NULL: not asked for) in one launch
+struct CopyOut {
+  swam_ctx* c;
+  CopyList list{};
+  void add(void* dst, size_t src_off, int64_t bytes) {
+    if (dst) list.add(c->arena + src_off, dst, bytes);
+  }
+  int run(const char* what) { return hip_check(c, launch_copy_list(list, c->st), what); }
+};
 
 void fill_alpha(int g, float* out) {
   // central half (|i - (g-1)/2| < g/4) weighs twice the outer quarters
@@ -700,11 +688,12 @@ int swam_score_reduce(swam_ctx* c, const float* s_all, float* q_out, float* v_ou
   if (rc != SWAM_OK) return rc;
   const swam_config& cf = c->cfg;
   const int64_t B = c->dv.n_scored;
-  if ((rc = copy_out(c, q_out, c->lay.q, B * cf.n_blocks * 4, "copy Q"))) return rc;
-  if ((rc = copy_out(c, v_out, c->lay.v, B * cf.n_frames * c->dv.n_s * 4, "copy V"))) return rc;
-  if ((rc = copy_out(c, a_out, c->lay.a, B * c->dv.n_s * 4, "copy A"))) return rc;
-  if ((rc = copy_out(c, core_out, c->lay.core, B * c->dv.k_eff * 4, "copy core"))) return rc;
-  return SWAM_OK;
+  CopyOut out{c};
+  out.add(q_out, c->lay.q, B * cf.n_blocks * 4);
+  out.add(v_out, c->lay.v, B * cf.n_frames * c->dv.n_s * 4);
+  out.add(a_out, c->lay.a, B * c->dv.n_s * 4);
+  out.add(core_out, c->lay.core, B * c->dv.k_eff * 4);
+  return out.run("copy Q, V, A");
 }
 
 int swam_select(swam_ctx* c, const float* v, const float* a, int32_t* keep_idx,
@@ -816,7 +805,11 @@ int swam_select_noalloc(int32_t batch, int32_t n_frames, int32_t n_s, int32_t n_
   s.keep = (int32_t*)(base + pool_b + core_b);
   s.keep_idx = keep_idx;
   s.keep_cnt = keep_cnt;
+  s.pack_pos = pack_pos;
+  s.gather = gather;
+  s.cu = cu_seqlens;
   s.B = batch;
+  s.batch = batch;
   s.F = n_frames;
   s.n_s = n_s;
   s.k_core = k_core;
@@ -834,8 +827,7 @@ int swam_select_noalloc(int32_t batch, int32_t n_frames, int32_t n_s, int32_t n_
   // every flag the kernels read is written by them first in the same call,
   // so the array's contents from an earlier call never matter
   const hipStream_t st = (hipStream_t)stream;
-  hipError_t e = launch_select(s, st);
-  if (e == hipSuccess) e = launch_packmap(s.keep, pack_pos, gather, cu_seqlens, batch, l_full, st);
+  const hipError_t e = launch_select(s, st);
   if (e != hipSuccess) return set_err(nullptr, SWAM_E_HIP, std::string("select: ") + hipGetErrorString(e));
   return SWAM_OK;
 }
@@ -877,18 +869,18 @@ int swam_export(swam_ctx* c, float* s_all, float* q, float* v, float* a, int32_t
   const int64_t B = cf.batch, F = cf.n_frames, n_s = c->dv.n_s;
   if ((keep_idx || keep_cnt || pack_pos || gather || cu_seqlens) && !c->sel_valid)
     return set_err(c, SWAM_E_STATE, "no selection cached");
-  int rc;
   const int64_t Bs = c->dv.n_scored;
-  if ((rc = copy_out(c, s_all, c->lay.s_all, Bs * cf.n_blocks * F * n_s * 4, "copy S"))) return rc;
-  if ((rc = copy_out(c, q, c->lay.q, Bs * cf.n_blocks * 4, "copy Q"))) return rc;
-  if ((rc = copy_out(c, v, c->lay.v, Bs * F * n_s * 4, "copy V"))) return rc;
-  if ((rc = copy_out(c, a, c->lay.a, Bs * n_s * 4, "copy A"))) return rc;
-  if ((rc = copy_out(c, keep_idx, c->lay.keep_idx, B * F * c->dv.k_max * 4, "copy keep_idx"))) return rc;
-  if ((rc = copy_out(c, keep_cnt, c->lay.keep_cnt, B * F * 4, "copy keep_cnt"))) return rc;
-  if ((rc = copy_out(c, pack_pos, c->lay.pack_pos, c->dv.rows_full * 4, "copy pack_pos"))) return rc;
-  if ((rc = copy_out(c, gather, c->lay.gather, c->dv.rows_full * 4, "copy gather"))) return rc;
-  if ((rc = copy_out(c, cu_seqlens, c->lay.cu_packed, (B + 1) * 4, "copy cu"))) return rc;
-  return SWAM_OK;
+  CopyOut out{c};
+  out.add(s_all, c->lay.s_all, Bs * cf.n_blocks * F * n_s * 4);
+  out.add(q, c->lay.q, Bs * cf.n_blocks * 4);
+  out.add(v, c->lay.v, Bs * F * n_s * 4);
+  out.add(a, c->lay.a, Bs * n_s * 4);
+  out.add(keep_idx, c->lay.keep_idx, B * F * c->dv.k_max * 4);
+  out.add(keep_cnt, c->lay.keep_cnt, B * F * 4);
+  out.add(pack_pos, c->lay.pack_pos, c->dv.rows_full * 4);
+  out.add(gather, c->lay.gather, c->dv.rows_full * 4);
+  out.add(cu_seqlens, c->lay.cu_packed, (B + 1) * 4);
+  return out.run("export");
 }
 
 int swam_pack(swam_ctx* c, const void* x_full, void* x_packed) {
