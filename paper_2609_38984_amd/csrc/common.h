@@ -81,6 +81,25 @@ __device__ __forceinline__ void store8(T* p, const float (&v)[8]) {
   }
 }
 
+// Weights that a later launch reads, touched by spare workgroups of this one so
+// that they come out of the caches there (p NULL: nothing to do).
+struct Prefetch {
+  const void* p = nullptr;
+  int64_t bytes = 0;
+};
+// workgroup wg of n reads its share of q, 8 16-byte loads per thread in flight
+__device__ __forceinline__ void prefetch_share(const Prefetch& q, int wg, int n) {
+  const uint4* w = (const uint4*)q.p;
+  const int64_t chunks = q.bytes / 16, step = (int64_t)n * blockDim.x;
+  for (int64_t i = (int64_t)wg * blockDim.x + threadIdx.x; i < chunks; i += 8 * step) {
+    uint4 v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = w[i + e * step < chunks ? i + e * step : i];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) asm volatile("" ::"v"(v[e].x), "v"(v[e].y), "v"(v[e].z), "v"(v[e].w));
+  }
+}
+
 __device__ __forceinline__ float warp_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);

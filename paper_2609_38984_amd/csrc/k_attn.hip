@@ -14,7 +14,7 @@
 //   1/8 scale folded into one FMA, tail-only masking and lazy rescaling.
 // fp32 path: 32 query rows of one head per workgroup, its four waves taking
 // every fourth 32-key tile, both products on 32x32x2 fp32 MFMAs.
-#include "common.h"
+#include "launchers.h"
 
 #include <type_traits>
 
@@ -46,12 +46,18 @@ typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 template <int NW, int WPE, int SUB>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
 attn_fwd_bf16(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,
-     const int32_t* __restrict__ cu, int n_seqs, int n_heads, int n_rows) {
+     const int32_t* __restrict__ cu, int n_seqs, int n_heads, int n_rows, int n_wg, const Prefetch pf0,
+     const Prefetch pf1) {
   constexpr int S = 2;                           // LDS stages (K and V tiles)
   constexpr int SK = SUB * ATT_BK;               // keys per stage: SUB tiles per barrier
   __shared__ uint4 Ks[S][SK * 8];                 // [key][8 chunks], chunk ^ lds_swz(key)
   __shared__ uint4 Vs[S][SK * 8];
-  const int nwg = gridDim.x, pid = blockIdx.x;
+  const int nwg = n_wg, pid = blockIdx.x;
+  if (pid >= nwg) {                              // spare workgroups past the grid's tiles
+    prefetch_share(pf0, pid - nwg, gridDim.x - nwg);
+    prefetch_share(pf1, pid - nwg, gridDim.x - nwg);
+    return;
+  }
   const int xcd = pid & 7, per = nwg >> 3, rem = nwg & 7;
   const int id = xcd * per + min(xcd, rem) + (pid >> 3);
   const int slots = nwg / n_heads;
@@ -367,7 +373,7 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ out, float* __re
 
 hipError_t launch_attention(int dtype, const void* qkv, void* o, float* lse,
                             const int32_t* cu_seqlens, int n_seqs, int64_t n_rows,
-                            int n_heads, hipStream_t st) {
+                            int n_heads, hipStream_t st, Prefetch pf0, Prefetch pf1) {
   if (n_rows <= 0) return hipSuccess;
   if (dtype == 1) {
     if (n_rows * 3 * (int64_t)n_heads * 64 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
@@ -381,9 +387,10 @@ hipError_t launch_attention(int dtype, const void* qkv, void* o, float* lse,
     const bf16_t* a = (const bf16_t*)qkv;
     bf16_t* ob = (bf16_t*)o;
     const int ni = (int)n_rows;
+    const int n_pf = pf0.p || pf1.p ? PREFETCH_WGS : 0;
 #define SWAM_ATT(NW_, WPE_, SUB_, SL_)                                                       \
-  hipLaunchKernelGGL((attn_fwd_bf16<NW_, WPE_, SUB_>), dim3((SL_) * n_heads), dim3(NW_ * 64), 0, \
-                     st, a, ob, lse, cu_seqlens, n_seqs, n_heads, ni)
+  hipLaunchKernelGGL((attn_fwd_bf16<NW_, WPE_, SUB_>), dim3((SL_) * n_heads + n_pf), dim3(NW_ * 64), \
+                     0, st, a, ob, lse, cu_seqlens, n_seqs, n_heads, ni, (SL_) * n_heads, pf0, pf1)
     // the 8-wave kernel stages 128 keys per barrier (64 KB of LDS, two
     // workgroups per CU); the 4-wave ones keep 64 so four fit on a CU
     if ((int64_t)(slots8 - n_seqs) * n_heads >= 7 * 64)

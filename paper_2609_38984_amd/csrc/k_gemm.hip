@@ -494,7 +494,7 @@ static hipError_t finish_splits(const float* ws, int splits, int M, int N, const
   if (ln == nullptr || N > LN_ROW_MAX)
     return run_epilogue<ROLE, T, EPI>(ws, splits, M, N, bias, gate, C, ldc, Cs, smap, st);
   ln->done = true;
-  return launch_splitk_ln(sizeof(T) == 2, ws, splits, M, N, bias, gate, C, ln->h, ln->shift, ln->scale, st);
+  return launch_splitk_ln(sizeof(T) == 2, ws, splits, M, N, bias, gate, C, ln->h, ln->shift, ln->scale, st, ln->pf);
 }
 
 // ln (out and down projections): a LayerNorm of the result into ln->h follows;

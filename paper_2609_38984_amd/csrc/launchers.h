@@ -44,6 +44,7 @@ enum GemmRole { ROLE_QKV = 0, ROLE_OUT = 1, ROLE_UP = 2, ROLE_DOWN = 3 };
 struct LnNext {
   void* h;
   const float *shift, *scale;
+  Prefetch pf = {};      // weights of the projection after it
   bool done = false;
 };
 hipError_t launch_gemm(int dtype, int role, const void* A, int64_t lda, const void* B,
@@ -69,9 +70,19 @@ struct AdalnArgs {
 hipError_t launch_adaln(int dtype, const AdalnArgs& a, int n_blk, const float* temb,
                         int d_temb, int d6, float* mod, hipStream_t st);
 
-// h[r] = LN(x[r]) (1 + scale) + shift
+// Token sets of at most SHORT_ROWS rows leave most CUs and the memory idle in
+// attention and LayerNorm and then wait for cold weights in the projections, so
+// PREFETCH_WGS spare workgroups of those launches read the weights ahead (192
+// rows, d = 1536, weights from memory / read ahead: QKV 11.1 / 7.9 us, up 14.2 /
+// 11.4, down 13.0 / 9.7, out 6.4 / 5.5; attention takes 2.1 us and LayerNorm 1.0
+// us longer.  Spare workgroups in the projections themselves cost them more than
+// they save: up 15.8 us).
+constexpr int SHORT_ROWS = 1024;
+constexpr int PREFETCH_WGS = 256;
+
+// h[r] = LN(x[r]) (1 + scale) + shift; pf: see above (bf16, up to SHORT_ROWS rows)
 hipError_t launch_ln_mod(int dtype, const void* x, void* h, const float* shift,
-                         const float* scale, int64_t rows, int d, hipStream_t st);
+                         const float* scale, int64_t rows, int d, hipStream_t st, Prefetch pf = {});
 // widest row that one workgroup's registers hold (the ln_row kernels)
 constexpr int LN_ROW_MAX = 4096;
 // the LayerNorm behind a projection whose K was split: x[r] += gate *
@@ -79,7 +90,8 @@ constexpr int LN_ROW_MAX = 4096;
 // part is [splits][rows][d], d <= LN_ROW_MAX
 hipError_t launch_splitk_ln(int dtype, const float* part, int splits, int64_t rows, int d,
                             const void* bias, const float* gate, void* x, void* h,
-                            const float* shift, const float* scale, hipStream_t st);
+                            const float* shift, const float* scale, hipStream_t st,
+                            Prefetch pf = {});
 // the same on gathered rows: xp[r] = x_full[gather[r]] (the gather-pack) and
 // h[r] = LN(xp[r]) (1 + scale) + shift, in one pass
 hipError_t launch_ln_mod_gather(int dtype, const void* x_full, const int32_t* gather, void* xp,
@@ -93,10 +105,10 @@ hipError_t launch_qk_post(int dtype, void* qkv, int64_t n_rows, int d, int pos_m
                           const float2* tab, int n_pos, int qk_norm, hipStream_t st);
 
 // o = softmax(q k^T / 8) v per head inside each sequence; lse (optional).
-// Sequence bounds are clamped to [0, n_rows].
+// Sequence bounds are clamped to [0, n_rows].  pf0, pf1 (bf16): weights read ahead.
 hipError_t launch_attention(int dtype, const void* qkv, void* o, float* lse,
                             const int32_t* cu_seqlens, int n_seqs, int64_t n_rows,
-                            int n_heads, hipStream_t st);
+                            int n_heads, hipStream_t st, Prefetch pf0 = {}, Prefetch pf1 = {});
 
 // Score kernels (mode A with lse, mode B computes lse first into lse_ws).
 struct ScoreArgs {

@@ -313,11 +313,13 @@ bool bad_block(const swam_block_weights* w) {
 // next_mod (blocks of a step): the modulation of the block that follows.  Its
 // first LayerNorm may share the pass that sums this block's split down
 // projection; *h_ready says so to that block's call, which then skips it.
+// next_w: that block's weights.
 int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* x,
               int64_t n_rows, const int32_t* cu, int n_seqs, float* lse_out, void* qkv,
               int pos_mode, const ScoreArgs* score = nullptr, const void* pack_src = nullptr,
               void* pruned_dst = nullptr, bool score_in_up = false, void* scatter_to = nullptr,
-              const float* next_mod = nullptr, bool* h_ready = nullptr) {
+              const float* next_mod = nullptr, bool* h_ready = nullptr,
+              const swam_block_weights* next_w = nullptr) {
   const int dt = c->cfg.dtype;
   const int64_t d = c->dv.d, hid = c->dv.hidden;
   void* h = c->ptr<char>(c->lay.h);
@@ -329,6 +331,11 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
   const float *sh1 = mod, *sc1 = mod + d, *g1 = mod + 2 * d;
   const float *sh2 = mod + 3 * d, *sc2 = mod + 4 * d, *g2 = mod + 5 * d;
   if (n_rows <= 0) return SWAM_OK;
+  // short token sets read the next projections' weights ahead of them
+  const bool ahead = dt == SWAM_BF16 && n_rows <= SHORT_ROWS;
+  auto read_ahead = [&](const void* p, int64_t elems) {
+    return ahead && p ? Prefetch{p, elems * c->dv.esz} : Prefetch{};
+  };
   if (pack_src) {
     {
       Timed t(c, SWAM_T_PACK);
@@ -367,8 +374,8 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
   }
   {
     Timed t(c, SWAM_T_ATTN);
-    SWAM_HIP(c, launch_attention(dt, qkv, o, lse_out, cu, n_seqs, n_rows, c->cfg.n_heads, st),
-             "attention");
+    SWAM_HIP(c, launch_attention(dt, qkv, o, lse_out, cu, n_seqs, n_rows, c->cfg.n_heads, st,
+                                 read_ahead(w->w_o, d * d), read_ahead(w->w_1, hid * d)), "attention");
   }
   if (score && !score_in_up) {
     // fork: the scores of this layer run on the side stream, concurrently
@@ -382,7 +389,7 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
     SWAM_HIP(c, hipEventRecord(c->ev_score, c->side), "scoring done");
     c->score_pending = true;
   }
-  LnNext ln2{h, sh2, sc2};
+  LnNext ln2{h, sh2, sc2, read_ahead(w->w_2, d * hid)};
   {
     Timed t(c, SWAM_T_GEMM_OUT);
     SWAM_HIP(c, launch_gemm(dt, ROLE_OUT, o, d, w->w_o, d, w->b_o, g1, x, d,
@@ -390,7 +397,7 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
   }
   if (!ln2.done) {
     Timed t(c, SWAM_T_LNMOD);
-    SWAM_HIP(c, launch_ln_mod(dt, x, h, sh2, sc2, n_rows, (int)d, st), "ln_mod 2");
+    SWAM_HIP(c, launch_ln_mod(dt, x, h, sh2, sc2, n_rows, (int)d, st, ln2.pf), "ln_mod 2");
   }
   if (score && score_in_up) {
     // this layer's q, k and lambda stay in place until the next block's QKV
@@ -403,7 +410,8 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
     SWAM_HIP(c, launch_gemm(dt, ROLE_UP, h, d, w->w_1, d, w->b_1, nullptr, u, hid, n_rows,
                             hid, d, st, sk, sk_n), "gemm up");
   }
-  LnNext ln1{h, next_mod, next_mod ? next_mod + d : nullptr};
+  LnNext ln1{h, next_mod, next_mod ? next_mod + d : nullptr,
+             read_ahead(next_w ? next_w->w_qkv : nullptr, 3 * d * d)};
   {
     Timed t(c, SWAM_T_GEMM_DOWN);
     SWAM_HIP(c, launch_gemm(dt, ROLE_DOWN, u, hid, w->w_2, hid, w->b_2, g2, x, d,
@@ -1037,7 +1045,8 @@ int enqueue_step_launches(swam_ctx* c, const swam_model* model, const void* x_fu
                      c->ptr<int32_t>(c->lay.cu_dense), cf.batch,
                      score ? c->ptr<float>(c->lay.lse) : nullptr, qkv, 0,
                      score ? &a : nullptr, nullptr, nullptr, in_up && l + 1 < cf.n_blocks, nullptr,
-                     l + 1 < cf.n_blocks ? mod + (int64_t)(l + 1) * 6 * d : nullptr, &h_ready);
+                     l + 1 < cf.n_blocks ? mod + (int64_t)(l + 1) * 6 * d : nullptr, &h_ready,
+                     l + 1 < cf.n_blocks ? &model->blocks[l + 1] : nullptr);
       if (rc != SWAM_OK) return rc;
     }
     if (score) {
@@ -1074,7 +1083,8 @@ int enqueue_step_launches(swam_ctx* c, const swam_model* model, const void* x_fu
                      c->ptr<int32_t>(c->lay.cu_packed), cf.batch, nullptr, qkv, 1, nullptr,
                      l == 0 ? x_full : nullptr, l == 0 && fork ? y_full : nullptr, false,
                      fold_unpack && last ? y_full : nullptr,
-                     last ? nullptr : mod + (int64_t)(l + 1) * 6 * d, &h_ready);
+                     last ? nullptr : mod + (int64_t)(l + 1) * 6 * d, &h_ready,
+                     last ? nullptr : &model->blocks[l + 1]);
       if (rc != SWAM_OK) return rc;
     }
     if (fork) SWAM_HIP(c, hipStreamWaitEvent(c->st, c->ev_score, 0), "join pruned-row copy");
