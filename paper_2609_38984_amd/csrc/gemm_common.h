@@ -21,6 +21,25 @@ __device__ __forceinline__ float epi_value(float acc, float bias, float gate, fl
   return resid + gate * (acc + bias);
 }
 
+// Rotary position of a row (0 without a table).  The kernels look the positions
+// of their rows up before the k loop: behind it, the index and the table are two
+// memory latencies in a row per slice of the store.
+__device__ __forceinline__ int qkpost_pos(int row, int M, const QkPost& qp) {
+  if (qp.tab == nullptr) return 0;
+  const int rr = min(row, M - 1);
+  int pos;
+  if (qp.pos_mode == 0) {
+    pos = rr % qp.l_full;
+  } else if (qp.pos_mode == 1) {
+    pos = qp.gather[rr] % qp.l_full;
+  } else {
+    int b = 0;
+    while (b + 1 < qp.n_seqs && qp.cu[b + 1] <= rr) ++b;
+    pos = rr - qp.cu[b];
+  }
+  return min(max(pos, 0), qp.n_pos - 1);
+}
+
 // Store of 8 consecutive QKV columns of one row with the QK-norm / rotary
 // embedding of q and k heads applied (the steps of qk_post_kernel on the
 // projection rounded to bf16).  The 8 lanes storing one row's 64 columns are
@@ -28,7 +47,7 @@ __device__ __forceinline__ float epi_value(float acc, float bias, float gate, fl
 // norm is a 3-step exchange; every lane takes part (the store is guarded).
 __device__ __forceinline__ void qkpost_store(const float* v, const bf16_t* __restrict__ bias,
                                              bf16_t* C, int64_t ldc, int row, int col, int col0,
-                                             int M, int N, const QkPost& qp) {
+                                             int M, int N, int pos, const QkPost& qp) {
   float x[8];
   {
     const float4 v0 = *reinterpret_cast<const float4*>(v);
@@ -57,18 +76,6 @@ __device__ __forceinline__ void qkpost_store(const float* v, const bf16_t* __res
       for (int e = 0; e < 8; ++e) x[e] *= r;
     }
     if (qp.tab != nullptr) {
-      const int rr = min(row, M - 1);
-      int pos;
-      if (qp.pos_mode == 0) {
-        pos = rr % qp.l_full;
-      } else if (qp.pos_mode == 1) {
-        pos = qp.gather[rr] % qp.l_full;
-      } else {
-        int b = 0;
-        while (b + 1 < qp.n_seqs && qp.cu[b + 1] <= rr) ++b;
-        pos = rr - qp.cu[b];
-      }
-      pos = min(max(pos, 0), qp.n_pos - 1);
       const float2* t = qp.tab + (int64_t)pos * 32 + ((col & 63) >> 1);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {

@@ -192,6 +192,16 @@ gemm_bf16_nt(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
+  constexpr int CPR = TN / 8;                         // 8-column runs per row of a wave's columns
+  constexpr int EP_IT = (32 * CPR + 63) / 64;         // runs per lane and 32-row slice
+  int pos[EPI == EPI_BIAS_QKPOST ? FM : 1][EP_IT];    // rotary positions of the lane's rows
+  if constexpr (EPI == EPI_BIAS_QKPOST)
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int it = 0; it < EP_IT; ++it)
+        pos[i][it] = qkpost_pos(m0 + wm * TM + i * 32 + (lane + 64 * it) / CPR, M, qp);
+
   constexpr int STAGE = (BM + BN) * 8;
   // k-stages of this workgroup: all of them, or split slice blockIdx.y of gridDim.y
   const int KT_all = K / GEMM_BK;
@@ -218,8 +228,6 @@ gemm_bf16_nt(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict
   // gate are loaded once, and each slice's residual rows are requested one
   // slice ahead (one exposed memory latency per tile, not one per slice).
   constexpr int EP_LD = TN + 4;                       // fp32 row pitch of the staging slice
-  constexpr int CPR = TN / 8;                         // 8-column runs per slice row
-  constexpr int EP_IT = (32 * CPR + 63) / 64;         // runs per lane and slice
   static_assert((32 * CPR) % 64 == 0, "every lane handles whole runs");
   static_assert(EPI != EPI_BIAS_QKPOST || TN == 64, "a wave's columns must be one head");
   static_assert(NW * 32 * EP_LD * 4 <= (int)sizeof(lds), "epilogue staging exceeds LDS");
@@ -271,7 +279,7 @@ gemm_bf16_nt(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict
       const int rl = (lane + 64 * it) / CPR;
       const int row = row0 + rl;
       if constexpr (EPI == EPI_BIAS_QKPOST) {
-        qkpost_store(stage + rl * EP_LD + cl, bias, C, ldc, row, col, col0, M, N, qp);
+        qkpost_store(stage + rl * EP_LD + cl, bias, C, ldc, row, col, col0, M, N, pos[i][it], qp);
         continue;
       }
       if (EPI == EPI_PARTIAL && row < M && col_ok) {
@@ -366,67 +374,60 @@ static hipError_t run_bf16(const void* A, int64_t lda, const void* B, int64_t ld
   }
 }
 
-// Tile and K-split choice: modelled time = rounds * (per-CU MFMA work of one
-// round / tile efficiency) + (split > 1) the partial-sum pass over HBM.  A
-// round places `per_cu` workgroups on each of the 256 CUs (LDS-limited).  The
-// 256x256 and 192x256 kernels fit one workgroup per CU and run in whole
-// rounds; two 128x128 workgroups share a CU and start as soon as a slot
-// frees, so their rounds count in halves once a grid spills past one slot per
-// CU.  The efficiencies are the per-CU MFMA rates of the kernels measured on
-// the block shapes of the d = 1536 and d = 2048 workloads, relative to the
-// 256x256 kernel (whose rate, about 40% of the per-CU peak, is the base; the
-// 192x256 tile, 8 waves of 96 x 64, runs at 0.85-0.92 of it and takes 0.85,
-// which makes it the choice where its 3/4-size tiles fill whole rounds: the
-// packed MLP up projection at 3,472 rows, the out and down projections at
-// 17,472 rows); the pass moves splits * M * N fp32 partials plus the bf16
-// output (and residual) at about 4 TB/s.  The 192x128 tile (8 waves of
-// 96 x 32, two workgroups per CU) enters at 0.83, which selects it where
-// half-rounds of its small tiles fill the CUs much better than the others:
-// the packed out projection at 3,472 rows and the d = 1024 projections at
-// 1,312 rows (measured 2-9% faster there).  At 0.84 it would also take the
-// packed down projection at 3,472 rows without a K split, measured 11%
-// slower than the three K slices.  (A 256x128 tile measured at 0.72 of the
-// base rate never won at any block shape from d = 256 to 4096 and was
-// dropped.)
+// Tile and K-split choice by modelled time: n rounds of a pipeline fill plus a
+// step per 64 columns of K, and the pass over the partial sums when K is split.
+// The 256x256 and 192x256 kernels fit one workgroup per CU and run in whole
+// rounds of 256; two 128x128 or 192x128 workgroups share a CU and start as soon
+// as a slot frees, so their rounds count in halves once a grid spills past one
+// slot per CU, and a lone workgroup per CU takes 0.6 of a shared round.  The
+// constants (us) are a fit to the four projections of d = 512, 1,088, 1,536 and
+// 2,048 at 16 row counts from 1,100 to 17,472: choosing by this model and the
+// ring kernel's runs within 0.5% of the best measured plan on average; one MFMA
+// efficiency per tile and no fill, as used before, lost 5.7% (out projection at
+// 1,400 x 1,536: 22.4 us on 128x128 tiles against 16.2 on the ring; down at
+// 3,688: 192x128 without a split 87 us, 192x256 with two slices 68.9 and a pass
+// that is the next LayerNorm's).
 struct GemmPlan { int tile, splits; bool ring; double us; };
 constexpr int GEMM_TILES = 4;
 static const int TILE_BM[GEMM_TILES] = {256, 128, 192, 192};
 static const int TILE_BN[GEMM_TILES] = {256, 128, 256, 128};
 static const int TILE_PER_CU[GEMM_TILES] = {1, 2, 1, 2};
-// wide_only: only tiles whose waves span 64 columns (the QK post-processing
-// store needs one head per wave)
-static GemmPlan choose_gemm(int64_t M, int64_t N, int64_t K, int64_t ws_floats,
+// wide_only: only tiles whose waves span 64 columns, without a split (the QK
+// post-processing store needs one head per wave); ln_follows: the pass over the
+// partial sums is the LayerNorm launch that follows anyway (3,472 x 1,536, three
+// slices: 14 us against the 7.5 us of the LayerNorm it replaces)
+static double split_pass_us(int splits, int64_t M, int64_t N, bool ln_follows) {
+  if (splits <= 1) return 0.0;
+  return ln_follows ? 0.5 + (double)splits * M * N * 4.0 / 5.0e6
+                    : 3.0 + (double)(splits + 1) * M * N * 4.0 / 5.0e6;
+}
+static GemmPlan choose_gemm(int64_t M, int64_t N, int64_t K, int64_t ws_floats, bool ln_follows,
                             bool wide_only = false) {
-  const double eff[GEMM_TILES] = {1.0, 0.80, 0.85, 0.83};
+  // 3 us of t0 stand for weights read cold, as the ring kernel's constants are
+  const double t0[GEMM_TILES] = {6.14, 6.15, 4.46, 5.81}, fill[GEMM_TILES] = {4.23, 5.66, 6.45, 5.03},
+               step[GEMM_TILES] = {1.55, 0.95, 1.209, 1.302}, lone[GEMM_TILES] = {1.0, 0.628, 1.0, 0.605};
   const int split_opts[6] = {1, 2, 3, 4, 6, 8};
   const int64_t kt = K / GEMM_BK;
-  const double cu_flops = 2.5e15 / 256.0 * 0.40;        // sustained MFMA rate per CU
-  GemmPlan best{0, 1, false, 0.0};
-  double best_t = 1e30;
+  GemmPlan best{0, 1, false, 1e30};
   for (int i = 0; i < GEMM_TILES; ++i) {
     if (wide_only && i == 3) continue;
-    const int bm = TILE_BM[i], bn = TILE_BN[i], per_cu = TILE_PER_CU[i];
-    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    const int64_t tiles = ((M + TILE_BM[i] - 1) / TILE_BM[i]) * ((N + TILE_BN[i] - 1) / TILE_BN[i]);
     for (int s : split_opts) {
-      if (s > 1 && (kt / s < 4 || (int64_t)s * M * N > ws_floats)) continue;
+      if (s > 1 && (wide_only || kt / s < 4 || (int64_t)s * M * N > ws_floats)) continue;
       const int64_t wgs = tiles * s;
-      double rounds;
-      if (per_cu == 1) {
-        rounds = (double)((wgs + 255) / 256);
-      } else {
-        // whole half-rounds while one slot per CU is not yet filled
-        rounds = std::max((double)wgs / (256.0 * per_cu),
-                          (double)((wgs + 255) / 256) / per_cu);
-      }
-      const double k_slice = (double)((kt + s - 1) / s) * GEMM_BK;
-      double t = rounds * 2.0 * bm * bn * per_cu * k_slice /
-                 (cu_flops * eff[i]);
-      if (s > 1) t += ((double)s * M * N * 4.0 + 4.0 * M * N) / 4.0e12 + 3e-6;
-      if (t < best_t) { best_t = t; best = {i, s, false, 0.0}; }
+      double n;
+      if (TILE_PER_CU[i] == 1) n = (double)((wgs + 255) / 256);
+      else if (wgs <= 256) n = lone[i];
+      else n = std::max((double)wgs / 512.0, (double)((wgs + 255) / 256) / 2.0);
+      double us = t0[i] + n * (fill[i] + step[i] * (double)((kt + s - 1) / s));
+      // alone, the smaller tiles are level with 256x256 at the same modelled time;
+      // within a step their extra operand traffic costs 3-5% (QKV at 12,059 rows:
+      // 202 us on 192x128 against 192)
+      if (i != 0) us *= 1.03;
+      us += split_pass_us(s, M, N, ln_follows);
+      if (us < best.us) best = {i, s, false, us};
     }
   }
-  // launch and pipeline fill on top of the model above (the fit of choose_ring)
-  best.us = 0.945e6 * best_t + 6.6;
   return best;
 }
 
@@ -458,8 +459,7 @@ static GemmPlan choose_ring(int dtype, int64_t M, int64_t N, int64_t K, int64_t 
       if (s > max_splits || (s > 1 && (kt / s < 4 || (int64_t)s * M * N > ws_floats))) continue;
       const int64_t n = (tiles * s + 255) / 256;
       double us = t0[i] + n * (fill[i] + step[i] * (double)((kt + s - 1) / s)) * (n > 1 ? 1.21 : 1.0);
-      if (s > 1)
-        us += (ln_follows ? 0.5 : 3.0) + ((double)s * M * N * 4.85 + 4.0 * M * N) / 4.0e6;
+      us += split_pass_us(s, M, N, ln_follows);
       if (us < best.us) best = {i, s, true, us};
     }
   }
@@ -469,7 +469,7 @@ static GemmPlan choose_ring(int dtype, int64_t M, int64_t N, int64_t K, int64_t 
 // the plan of one bf16 projection; ln_follows: a LayerNorm of the result is
 // next (out and down projections)
 static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t ws_floats, bool ln_follows) {
-  const GemmPlan c = choose_gemm(M, N, K, ws_floats);
+  const GemmPlan c = choose_gemm(M, N, K, ws_floats, ln_follows);
   const GemmPlan r = choose_ring(1, M, N, K, ws_floats, ln_follows, 8);
   return r.us < c.us ? r : c;
 }
@@ -541,7 +541,7 @@ static int scored_idle_slots(const GemmPlan& p, int64_t M, int64_t N) {
 // it is taken only where it saves more than the events that the scoring on
 // the side stream needs instead (about 8 us)
 static GemmPlan plan_up_scored(int64_t M, int64_t N, int64_t K, int64_t ws_floats) {
-  const GemmPlan p = plan_gemm(M, N, K, ws_floats, false), c = choose_gemm(M, N, K, ws_floats);
+  const GemmPlan p = plan_gemm(M, N, K, ws_floats, false), c = choose_gemm(M, N, K, ws_floats, false);
   return p.ring && scored_idle_slots(c, M, N) > 0 && c.us < p.us + 8.0 ? c : p;
 }
 
@@ -629,20 +629,18 @@ hipError_t launch_gemm_qkv(int dtype, const void* A, int64_t lda, const void* B,
   if (M <= 0) return hipSuccess;
   const bool post = qp.qk_norm || qp.tab != nullptr;
   if (dtype == 1 && post) {
-    const GemmPlan p = choose_gemm(M, N, K, ws ? ws_floats : 0, true);
+    const GemmPlan p = choose_gemm(M, N, K, 0, false, true);
     const int m = (int)M, n = (int)N, k = (int)K;
     const GemmPlan r = choose_ring(1, M, N, K, 0, false, 1);
     if (r.us < p.us) {
       const RingArgs a{A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, nullptr, qp, nullptr, nullptr};
       return launch_ring(1, ROLE_QKV, a, {r.tile, 1}, st);
     }
-    if (p.splits <= 1) {
-      if (p.tile == 0)
-        return run_bf16<ROLE_QKV, 256, 256, 2, 4, EPI_BIAS_QKPOST>(A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, 1, nullptr, st, qp);
-      if (p.tile == 2)
-        return run_bf16<ROLE_QKV, 192, 256, 2, 4, EPI_BIAS_QKPOST>(A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, 1, nullptr, st, qp);
-      return run_bf16<ROLE_QKV, 128, 128, 2, 2, EPI_BIAS_QKPOST>(A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, 1, nullptr, st, qp);
-    }
+    if (p.tile == 0)
+      return run_bf16<ROLE_QKV, 256, 256, 2, 4, EPI_BIAS_QKPOST>(A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, 1, nullptr, st, qp);
+    if (p.tile == 2)
+      return run_bf16<ROLE_QKV, 192, 256, 2, 4, EPI_BIAS_QKPOST>(A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, 1, nullptr, st, qp);
+    return run_bf16<ROLE_QKV, 128, 128, 2, 2, EPI_BIAS_QKPOST>(A, lda, B, ldb, bias, nullptr, C, ldc, m, n, k, 1, nullptr, st, qp);
   }
   const hipError_t e = launch_gemm(dtype, ROLE_QKV, A, lda, B, ldb, bias, nullptr, C, ldc, M, N, K,
                                    st, ws, ws_floats);

@@ -128,6 +128,13 @@ gemm_ring(const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t
   float gg[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   constexpr int VEC = (int)sizeof(T) / 2;             // 16-byte pieces of a run
   uint4 bw[VEC], res[2][RUNS][VEC];                   // unconverted: nothing waits for them yet
+  int pos[2][RUNS];                                   // rotary positions of the lane's rows
+  if constexpr (EPI == EPI_BIAS_QKPOST)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int it = 0; it < RUNS; ++it)
+        pos[i][it] = qkpost_pos(m0 + wm * 64 + i * 32 + (wk * RUNS + it) * 8 + (lane >> 3), M, qp);
   if constexpr (EPI != EPI_PARTIAL && EPI != EPI_BIAS_QKPOST) {
 #pragma unroll
     for (int p = 0; p < VEC; ++p)
@@ -219,7 +226,7 @@ gemm_ring(const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t
       }
       if constexpr (EPI == EPI_BIAS_QKPOST) {
         static_assert(sizeof(T) == 2, "the QK post-processing store is bf16");
-        qkpost_store(v, bias, C, ldc, row, col, n0 + wn * 64, M, N, qp);
+        qkpost_store(v, bias, C, ldc, row, col, n0 + wn * 64, M, N, pos[i][it], qp);
       } else if (row < M && col_ok) {
         if constexpr (EPI == EPI_PARTIAL) {
           float* q = part + ((int64_t)z * M + row) * N + col;

@@ -56,7 +56,7 @@ hipError_t launch_gemm(int dtype, int role, const void* A, int64_t lda, const vo
 // QKV projection C = A . B^T + bias followed by the QK-norm / rotary
 // embedding of qp on its q and k columns, with the same bf16 rounding of the
 // projection as launch_gemm + launch_qk_post; fused into the GEMM's store
-// for bf16 unless the shape splits K (then the two launches).
+// for bf16 (which then does not split K), two launches for fp32.
 hipError_t launch_gemm_qkv(int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                            const void* bias, void* C, int64_t ldc, int64_t M, int64_t N,
                            int64_t K, const QkPost& qp, hipStream_t st, float* ws = nullptr,
