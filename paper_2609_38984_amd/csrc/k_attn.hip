@@ -43,15 +43,20 @@ typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 // NW waves x 32 query rows per workgroup; WPE = minimum waves per SIMD the
 // register allocation must allow (4 caps it at 128 VGPRs); SUB 64-key tiles
 // share one LDS stage, i.e. one barrier and one DMA wait.
-template <int NW, int WPE, int SUB>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
+// KS = 2: two groups of NW waves take every other stage of keys for the same
+// query rows, each with its own stage buffers; their (max, sum, O) are merged
+// through LDS in group order.  A workgroup alone on its CU is bound by the
+// serial chain over its key tiles (one wave per SIMD hides neither the LDS
+// reads nor the exponentials), so half the chain is worth the merge: 1,312
+// rows x 16 heads 21.7 -> 18.5 us, 2,686 x 12 40.4 -> 33.1; four groups: 20.9.
+template <int NW, int WPE, int SUB, int KS>
+__global__ void __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
 attn_fwd_bf16(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,
      const int32_t* __restrict__ cu, int n_seqs, int n_heads, int n_rows, int n_wg, const Prefetch pf0,
      const Prefetch pf1) {
   constexpr int S = 2;                           // LDS stages (K and V tiles)
   constexpr int SK = SUB * ATT_BK;               // keys per stage: SUB tiles per barrier
-  __shared__ uint4 Ks[S][SK * 8];                 // [key][8 chunks], chunk ^ lds_swz(key)
-  __shared__ uint4 Vs[S][SK * 8];
+  __shared__ uint4 kv[2][KS][S][SK * 8];          // K | V: [key][8 chunks], chunk ^ lds_swz(key)
   const int nwg = n_wg, pid = blockIdx.x;
   if (pid >= nwg) {                              // spare workgroups past the grid's tiles
     prefetch_share(pf0, pid - nwg, gridDim.x - nwg);
@@ -67,7 +72,10 @@ attn_fwd_bf16(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* _
   if (!find_tile<BQ>(cu, n_seqs, n_rows, id - h * slots, s0, s1, q0)) return;
   const int d = n_heads * 64;
   const int64_t ld = 3 * (int64_t)d;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) % NW;
+  const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 6) / NW);   // key group
+  uint4 (&Ks)[S][SK * 8] = kv[0][kg];
+  uint4 (&Vs)[S][SK * 8] = kv[1][kg];
   const int g = lane >> 5;
   const int qrow = q0 + wave * 32 + (lane & 31);
   const bool qvalid = qrow < s1;
@@ -133,9 +141,7 @@ attn_fwd_bf16(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* _
   float m_run = -1e30f, l_run = 0.0f;
   const float sc = 1.4426950408889634f * 0.125f;
   const int nkt = (s1 - s0 + SK - 1) / SK;       // stages
-#pragma unroll
-  for (int p = 0; p < S - 1; ++p)
-    if (p < nkt) issue(p, s0 + p * SK);
+  if (kg < nkt) issue(0, s0 + kg * SK);
   // one 64-key tile of stage buffer `cur` at key offset sub * 64; full tiles
   // carry no masking code, the ragged last one runs a copy with the key mask
   auto tile = [&](int cur, int sub, int kb, auto masked) {
@@ -231,14 +237,18 @@ attn_fwd_bf16(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* _
         }
     }
   };
-  auto stage = [&](int kt, auto masked) {
-    const int cur = kt % S;
+  // iteration `it` of this group: stage it * KS + kg (none past the last one,
+  // but every group keeps the barriers)
+  static_assert(S == 2, "the prefetch goes to the other buffer");
+  auto stage = [&](int it, auto masked) {
+    const int cur = it & 1, kt = it * KS + kg;
     const int kb = s0 + kt * SK;
     // stage kt has landed (own DMA done, then everyone's via the barrier); the
     // barrier also releases the stage the next prefetch overwrites
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (kt + S - 1 < nkt) issue((kt + S - 1) % S, kb + (S - 1) * SK);
+    if (kt + KS < nkt) issue(cur ^ 1, kb + KS * SK);
+    if (KS > 1 && kt >= nkt) return;
 #pragma unroll
     for (int sub = 0; sub < SUB; ++sub) {
       const int kbs = kb + sub * ATT_BK;
@@ -249,10 +259,49 @@ attn_fwd_bf16(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* _
       }
     }
   };
-  const int nfull = (s1 - s0) / SK;
-  for (int kt = 0; kt < nfull; ++kt) stage(kt, std::false_type{});
-  if (nfull < nkt) stage(nfull, std::true_type{});
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  const int nfull = (s1 - s0) / SK / KS;          // iterations in which every stage is full
+  const int nit = (nkt + KS - 1) / KS;
+  for (int it = 0; it < nfull; ++it) stage(it, std::false_type{});
+  for (int it = nfull; it < nit; ++it) stage(it, std::true_type{});
+  float l_tot = l_run + __shfl_xor(l_run, 32);
+  if constexpr (KS > 1) {
+    // groups 1.. park their sums, group 0 adds them up in order
+    constexpr int SLOT = 34 * 64;                 // floats per wave
+    static_assert((KS - 1) * NW * SLOT * 4 <= (int)sizeof(kv), "merge space");
+    float* ex = reinterpret_cast<float*>(kv);
+    __syncthreads();                              // the last stages are consumed
+    if (kg > 0) {
+      float* e = ex + ((kg - 1) * NW + wave) * SLOT + lane;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) e[(16 * t + r) * 64] = o[t][r];
+      e[32 * 64] = m_run;
+      e[33 * 64] = l_tot;
+    }
+    __syncthreads();
+    if (kg > 0) return;
+    float mx = m_run;
+#pragma unroll
+    for (int k = 0; k < KS - 1; ++k) mx = fmaxf(mx, ex[(k * NW + wave) * SLOT + 32 * 64 + lane]);
+    const float f0 = __builtin_amdgcn_exp2f(m_run - mx);
+    l_tot *= f0;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[t][r] *= f0;
+#pragma unroll
+    for (int k = 0; k < KS - 1; ++k) {
+      const float* e = ex + (k * NW + wave) * SLOT + lane;
+      const float f = __builtin_amdgcn_exp2f(e[32 * 64] - mx);   // 0 for a group without keys
+      l_tot = fmaf(e[33 * 64], f, l_tot);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[t][r] = fmaf(e[(16 * t + r) * 64], f, o[t][r]);
+    }
+    m_run = mx;
+  }
   if (!qvalid) return;
   const float inv = 1.0f / l_tot;
   bf16_t* op = out + (int64_t)qrow * d + h * 64;
@@ -377,28 +426,46 @@ hipError_t launch_attention(int dtype, const void* qkv, void* o, float* lse,
   if (n_rows <= 0) return hipSuccess;
   if (dtype == 1) {
     if (n_rows * 3 * (int64_t)n_heads * 64 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    // 8 waves (256 query rows) share each K/V tile when the grid gives the
-    // CUs at least 1.75 such workgroups on average (measured: 3,744 packed
-    // rows x 32 heads, 480 workgroups, run 11% faster than with 4 waves;
-    // 3,472 x 24, 336 workgroups, 7% slower); otherwise 4 waves, with the
-    // 4-waves/SIMD register cap only when enough workgroups exist to use it.
-    const int slots8 = (int)((n_rows + 255) / 256) + n_seqs;
-    const int slots4 = (int)((n_rows + 127) / 128) + n_seqs;
+    // Four shapes, by how many workgroups of 64, 128 or 256 query rows there
+    // are (at most, the lengths being on the device) and the mean length:
+    //  - as long as every workgroup has a CU of its own, a key split, with the
+    //    smallest row tile that still leaves it one (us; 64-row tiles split |
+    //    128 split | 128 unsplit): 400 rows x 24 heads 8.3 | 10.0 | 10.2,
+    //    1,312 x 8 14.6 | 17.6 | 20.8, 1,312 x 16 (336 tiles of 64 rows) 20.8 |
+    //    18.7 | 22.2.  128-row tiles below 384 rows per sequence have too few
+    //    keys to split (326 x 24: 9.3 | 9.3, 192 x 24: 7.7 | 7.0);
+    //  - more workgroups of 128 rows than CUs but not of 256: 8 waves, so that
+    //    no CU runs two in turn (8 waves | 4 waves: 1,312 x 28 27.4 | 29.5,
+    //    2,400 x 24 47.6 | 51.1, 8,000 x 8 145 | 158; level at 600 x 64,
+    //    17.4 | 17.3, and slower below, 375 x 10 x 8 sequences 14.1 | 13.5);
+    //  - 8 waves again from 1.75 such workgroups per CU (3,744 rows x 32 heads,
+    //    480 workgroups, 11% faster than 4 waves);
+    //  - 4 waves between (2,600 x 24, 264 workgroups of 256 rows, 57 us against
+    //    81; 3,472 x 24 102 against 111).
+    const int64_t ns = n_seqs;
+    const int slots8 = (int)((n_rows + 255 * ns) / 256);
+    const int slots4 = (int)((n_rows + 127 * ns) / 128);
+    const int slots2 = (int)((n_rows + 63 * ns) / 64);
+    const int64_t len = n_rows / ns;
     const bf16_t* a = (const bf16_t*)qkv;
     bf16_t* ob = (bf16_t*)o;
     const int ni = (int)n_rows;
     const int n_pf = pf0.p || pf1.p ? PREFETCH_WGS : 0;
-#define SWAM_ATT(NW_, WPE_, SUB_, SL_)                                                       \
-  hipLaunchKernelGGL((attn_fwd_bf16<NW_, WPE_, SUB_>), dim3((SL_) * n_heads + n_pf), dim3(NW_ * 64), \
-                     0, st, a, ob, lse, cu_seqlens, n_seqs, n_heads, ni, (SL_) * n_heads, pf0, pf1)
+#define SWAM_ATT(NW_, WPE_, SUB_, KS_, SL_)                                                   \
+  hipLaunchKernelGGL((attn_fwd_bf16<NW_, WPE_, SUB_, KS_>), dim3((SL_) * n_heads + n_pf),      \
+                     dim3(NW_ * KS_ * 64), 0, st, a, ob, lse, cu_seqlens, n_seqs, n_heads, ni, \
+                     (SL_) * n_heads, pf0, pf1)
     // the 8-wave kernel stages 128 keys per barrier (64 KB of LDS, two
     // workgroups per CU); the 4-wave ones keep 64 so four fit on a CU
-    if ((int64_t)(slots8 - n_seqs) * n_heads >= 7 * 64)
-      SWAM_ATT(8, 4, 2, slots8);
-    else if ((int64_t)(slots4 - n_seqs) * n_heads >= 3 * 256)
-      SWAM_ATT(4, 4, 1, slots4);
+    if ((int64_t)slots2 * n_heads <= 256)
+      SWAM_ATT(2, 4, 1, 2, slots2);
+    else if ((int64_t)slots4 * n_heads <= 256 && len >= 384)
+      SWAM_ATT(4, 1, 1, 2, slots4);
+    else if (((int64_t)slots4 * n_heads > 256 && (int64_t)slots8 * n_heads <= 256 && len >= 800) ||
+             (n_rows + 255) / 256 * n_heads >= 7 * 64)
+      SWAM_ATT(8, 4, 2, 1, slots8);
     else
-      SWAM_ATT(4, 1, 1, slots4);
+      SWAM_ATT(4, 4, 1, 1, slots4);
 #undef SWAM_ATT
   } else {
     hipLaunchKernelGGL(attn_fwd_f32, dim3((unsigned)((n_rows + 31) / 32 + n_seqs), n_heads), dim3(256),

@@ -79,3 +79,28 @@ def test_step_chains_the_layer_norms(heads, rows, dtype):
     err = maxrel(host(y), want)
     print(f"  max-rel {err:.2e}", flush=True)
     assert err < TOL[dtype]
+
+
+@pytest.mark.parametrize("heads,cu", [
+    (4, [0, 1, 1, 2]), (8, [0, 63, 128, 193]), (1, [0, 65]), (12, [0, 1312]),   # 64-row tiles, keys split
+    (16, [0, 1312]), (16, [0, 384, 384, 1153]), (12, [0, 130, 1500]),           # 128-row tiles, keys split
+    (16, [0, 200, 200, 330, 1100]), (20, [0, 600, 1300, 1999]),                 # 128-row tiles
+    (16, [0, 1312, 2500]), (13, [0, 2561])])                                    # 256-row tiles
+def test_block_attention_shapes(heads, cu):
+    """Every shape the bf16 attention is dispatched in, with sequences shorter
+    than a tile of keys, empty ones and lengths at the edges of the tiles."""
+    from paper_2609_38984_amd import swam
+    rows = cu[-1]
+    cfg = _cfg(heads, max(rows, 3), dtype="bf16")
+    blocks, dblocks, _ = model_for(cfg, 1)
+    x = W.make_inputs(cfg, blocks[0]["w_qkv"]).x(0)[:rows]
+    temb = W.timestep_embedding(cfg, 0)
+    want, _ = O.block(x, blocks[0], temb, np.array(cu, np.int32), heads, cfg.dtype)
+    ctx = swam.Context(cfg)
+    y = dev(x, act_dtype(cfg))
+    print(f"attention of {heads} heads, sequences {cu}", flush=True)
+    ctx.block(dblocks[0], dev(temb), y, rows, dev(np.array(cu, np.int32)), len(cu) - 1)
+    torch.cuda.synchronize()
+    err = maxrel(host(y), want)
+    print(f"  max-rel {err:.2e}", flush=True)
+    assert err < TOL["bf16"]
