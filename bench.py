@@ -239,7 +239,7 @@ def kernel_class(name):
     m = re.search(r"(?:gemm_bf16_nt|gemm_ring|splitk_epilogue)<(\d+)", name)
     if m:
         return GEMM_CLASSES[int(m.group(1))]
-    if re.search(r"ln_mod_bf16<\d+, true>", name) or "pack_rows" in name:
+    if re.search(r"ln_mod_bf16<\d+, true>|ln_row<[^>]*, 1>", name) or "pack_rows" in name:
         return "PACK"
     for sub, cls in (("attn_fwd", "ATTN"), ("score_bf16", "SCORE"), ("score_f32", "SCORE"),
                      ("unpack_", "UNPACK")):
@@ -250,13 +250,19 @@ def kernel_class(name):
 
 def class_units(rows, cls):
     """Launch units of one class in stream order from (id, name, duration) rows:
-    [duration, [ids]], a split-K partial launch and its epilogue being one unit
-    (one projection)."""
-    units = []
+    [duration, [ids]], a split-K partial launch and the pass over its sums (an
+    epilogue, or the next LayerNorm) being one unit (one projection)."""
+    units, gemm = [], None
     for rid, name, dur in rows:
-        if kernel_class(name) != cls:
+        k = kernel_class(name)
+        if k in GEMM_CLASSES:
+            gemm = k
+        sums = "splitk_epilogue" in name
+        if re.search(r"ln_row<[^>]*, 2>", name):
+            k, sums = gemm, True
+        if k != cls:
             continue
-        if "splitk_epilogue" in name and units:
+        if sums and units:
             units[-1][0] += dur
             units[-1][1].append(rid)
         else:

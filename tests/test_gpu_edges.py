@@ -122,3 +122,30 @@ def test_partially_overlapping_output_is_rejected():
         assert e.value.code == -1 and "overlap" in str(e.value)
     torch.cuda.synchronize()
     assert bool((buf == 0).all())
+
+
+def test_exports_to_unaligned_buffers():
+    """Exports into buffers that start between 16-byte boundaries (their copy
+    then moves words) hold the bytes of the aligned ones, and nothing around
+    them changes."""
+    from paper_2609_38984_amd import swam
+    cfg = BASE.replace(frame_h=3, frame_w=7, k_core=5, k_anchor=3)
+    blocks, _, model = model_for(cfg)
+    inp = W.make_inputs(cfg, blocks[0]["w_qkv"])
+    ctx = swam.Context(cfg)
+    x = dev(inp.x(0))
+    ctx.step(model, x, dev(inp.temb(0)), 0, torch.empty_like(x))
+    n_v, k = cfg.batch * cfg.n_frames * cfg.n_s, cfg.k_core + cfg.k_anchor
+    sizes = dict(v=(n_v, torch.float32), a=(cfg.batch * cfg.n_s, torch.float32),
+                 keep_idx=(cfg.batch * cfg.n_frames * k, torch.int32),
+                 pack_pos=(cfg.batch * cfg.l_full, torch.int32), cu_seqlens=(cfg.batch + 1, torch.int32))
+    want = {name: torch.full((n,), -7, dtype=t, device="cuda:0") for name, (n, t) in sizes.items()}
+    ctx.export(**want)
+    for off in (1, 2, 3):
+        bufs = {name: torch.full((n + 8,), -7, dtype=t, device="cuda:0") for name, (n, t) in sizes.items()}
+        ctx.export(**{name: b[off:off + sizes[name][0]] for name, b in bufs.items()})
+        torch.cuda.synchronize()
+        for name, b in bufs.items():
+            n = sizes[name][0]
+            assert torch.equal(b[off:off + n], want[name]), (name, off)
+            assert bool((b[:off] == -7).all()) and bool((b[off + n:] == -7).all()), (name, off)
