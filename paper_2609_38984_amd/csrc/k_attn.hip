@@ -16,6 +16,7 @@
 // every fourth 32-key tile, both products on 32x32x2 fp32 MFMAs.
 #include "launchers.h"
 
+#include <cfloat>
 #include <type_traits>
 
 namespace swam {
@@ -352,7 +353,10 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ out, float* __re
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[t][r] = 0.0f;
-  float m = -INFINITY, l = 0.0f;
+  // the running max starts at the lowest finite value: a first tile whose
+  // logits are all minus infinity then adds nothing, where (-inf) - (-inf)
+  // would make the wave's sums NaN
+  float m = -FLT_MAX, l = 0.0f;
   for (int kb = s0 + 32 * wave; kb < s1; kb += 128) {
     const float* kp = kbase + (int64_t)min(kb + r31, s1 - 1) * ld;
     f32x4 kf[8];
@@ -409,7 +413,7 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ out, float* __re
   float lt = 0.0f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const float f = expf(ms[w][q] - mt);         // 0 for a wave without keys
+    const float f = expf(ms[w][q] - mt);         // 0 for a wave without finite logits
     lt = fmaf(ls[w][q], f, lt);
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = fmaf(os[w][q][c + e], f, acc[e]);

@@ -1,0 +1,62 @@
+"""Infinite and NaN values on the GPU where they have a defined effect: a key
+whose logit overflows to minus infinity takes no part in the softmax of its
+sequence, wherever the attention's key tiles and waves put it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import workload as W
+from helpers import act_dtype, dev, host, maxrel, model_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+
+
+TOL = {"bf16": 2e-2, "f32": 1e-4}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("heads,cu", [(1, [0, 2]), (1, [0, 33]), (2, [0, 65]), (1, [0, 97, 226]), (3, [0, 128, 161])])
+def test_logit_of_minus_infinity(heads, cu, dtype):
+    """The last key of every sequence overflows every query's logit to minus
+    infinity.  In these lengths it is alone in its tile of 32 or 64 keys (or
+    the last of a full one), so it is all that one of the waves that share
+    the keys sees.  Every other key has logit 0, exactly."""
+    from paper_2609_38984_amd import swam
+    rows, d = cu[-1], 64 * heads
+    cfg = W.preset(1).replace(d_model=d, n_heads=heads, n_blocks=1, n_ctx=max(rows - 3, 0), n_frames=1,
+                              frame_h=1, frame_w=2, n_act=1, k_core=1, k_anchor=0, dtype=dtype)
+    w = W.block_weights(cfg, 0)
+    rng = np.random.default_rng(5)
+    # rows of pairs (a, -a): their mean is 0 without rounding, so the first pair, zero in
+    # every row but the last of a sequence, stays zero behind the LayerNorm
+    a = np.round(rng.uniform(0.5, 2.0, (rows, d // 2)) * 64) / 64
+    a[:, 0] = 0.0
+    a[np.array(cu[1:]) - 1, 0] = 2.0
+    x = np.stack([a, -a], -1).reshape(rows, d).astype(np.float32)
+    w["w_ada"] = np.zeros_like(w["w_ada"])
+    w["b_ada"] = np.repeat(np.array([0, 0, 1, 0, 0, 1], np.float32), d)
+    w["w_qkv"][:2 * d] = 0.0
+    w["b_qkv"][:2 * d] = 0.0
+    big = float(2 ** 66)
+    for h in range(heads):
+        w["b_qkv"][64 * h] = -big                  # q . k / 8 = -2^129 a or less at the last key
+        w["w_qkv"][d + 64 * h, :2] = [big, -big]
+    temb = W.timestep_embedding(cfg, 0)
+    want, _ = O.block(x, w, temb, np.array(cu, np.int32), heads, cfg.dtype)
+    dw = {k: dev(v, act_dtype(cfg)) for k, v in w.items()}
+    ctx = swam.Context(cfg)
+    y = dev(x, act_dtype(cfg))
+    lse = torch.full((rows, heads), 7.0, device="cuda:0")
+    ctx.block(dw, dev(temb), y, rows, dev(np.array(cu, np.int32)), len(cu) - 1, lse_out=lse)
+    torch.cuda.synchronize()
+    n = np.repeat(np.diff(cu), np.diff(cu))
+    np.testing.assert_allclose(host(lse), np.repeat(np.log(n - 1.0)[:, None], heads, 1), atol=2e-6 * np.log(rows) + 1e-6)
+    assert maxrel(host(y), want) < TOL[dtype]
