@@ -56,7 +56,9 @@ score_f32(const float* __restrict__ q, int64_t q_seq, int64_t q_row,
     for (int e = 0; e < 16; ++e) x = fmaf(qr[h * 64 + e], kr[h * 64 + e], x);
     x += __shfl_xor(x, 16);
     x += __shfl_xor(x, 32);
-    s += aw * expf(x * 0.125f - lr[h]);
+    // a padding slot repeats the last query: its term is left out, not weighted
+    // by zero, so that an overflow there stays the infinity it is
+    if (a < g) s += aw * expf(x * 0.125f - lr[h]);
   }
   // sum over the query slots (the four quarters hold the same sums)
   s += __shfl_xor(s, 8);

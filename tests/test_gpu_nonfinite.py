@@ -60,3 +60,37 @@ def test_logit_of_minus_infinity(heads, cu, dtype):
     n = np.repeat(np.diff(cu), np.diff(cu))
     np.testing.assert_allclose(host(lse), np.repeat(np.log(n - 1.0)[:, None], heads, 1), atol=2e-6 * np.log(rows) + 1e-6)
     assert maxrel(host(y), want) < TOL[dtype]
+
+
+@pytest.mark.parametrize("heads,n_s", [(1, 5), (3, 17), (2, 64)])
+@pytest.mark.parametrize("g", [1, 2, 3, 4, 5, 8, 11, 16])
+def test_fp32_scores_and_their_overflow(g, heads, n_s):
+    """fp32 scores of every size of the query group, as the oracle's; with a
+    normaliser so low that the last query of the first frame overflows, that
+    frame's scores are infinite, not NaN, and the others unchanged."""
+    from paper_2609_38984_amd import swam
+    frames, d = 3, 64 * heads
+    cfg = W.preset(1).replace(d_model=d, n_heads=heads, n_blocks=1, n_ctx=2, n_frames=frames, frame_h=1,
+                              frame_w=n_s, n_act=g * frames, k_core=1, k_anchor=0, dtype="f32", batch=2)
+    rng = np.random.default_rng(100 * g + n_s)
+    q = rng.standard_normal((2, g * frames, d)).astype(np.float32)
+    k = rng.standard_normal((2, frames * n_s, d)).astype(np.float32)
+    lse = rng.uniform(3.0, 6.0, (2, heads, g * frames)).astype(np.float32)
+    want = np.stack([O.score(q[b], k[b], lse[b].T, frames, n_s, heads) for b in range(2)])
+    ctx = swam.Context(cfg)
+    dq, dk = dev(q), dev(k)
+
+    def run(lam):
+        s = torch.full((2, frames, n_s), -1.0, device="cuda:0")
+        ctx.score(dq, g * frames * d, d, dk, frames * n_s * d, d, s, lse_act=dev(lam.transpose(0, 2, 1)))
+        torch.cuda.synchronize()
+        return host(s)
+
+    got = run(lse)
+    # a sum of g * heads products of exponentials of fp32 logits (64 products of N(0, 1) each)
+    np.testing.assert_allclose(got, want, rtol=2e-5)
+    lse[1, 0, g - 1] = -200.0
+    low = run(lse)
+    assert np.isposinf(low[1, 0]).all()
+    np.testing.assert_array_equal(low[0], got[0])
+    np.testing.assert_array_equal(low[1, 1:], got[1, 1:])
