@@ -281,7 +281,9 @@ reduce_maps(const float* __restrict__ s_all, const double* __restrict__ fsum,
     double dc = 0.0, da = 0.0;
     for (int m = 0; m < L; ++m) {
       if (flag[m]) {
-        if (blockIdx.x == 0) core[b * k_eff + n] = m;
+        // a NaN quality outranks none and is outranked by none, so more than
+        // k_eff layers may be flagged: the list holds the first k_eff
+        if (blockIdx.x == 0 && n < k_eff) core[b * k_eff + n] = m;
         ++n;
         dc += qv[m];
       }

@@ -94,3 +94,39 @@ def test_fp32_scores_and_their_overflow(g, heads, n_s):
     assert np.isposinf(low[1, 0]).all()
     np.testing.assert_array_equal(low[0], got[0])
     np.testing.assert_array_equal(low[1, 1:], got[1, 1:])
+
+
+@pytest.mark.parametrize("layers,k_layer,n_s", [(64, 6, 40), (64, 32, 64), (9, 1, 70)])
+def test_nan_scores_stay_in_their_sequence(layers, k_layer, n_s):
+    """Layers of NaN quality: every one of them ranks among the core layers, so
+    more than K_layer do.  The sequences beside it keep their bits, the core
+    layers stay K_layer a sequence, and its own V is NaN."""
+    from paper_2609_38984_amd import swam
+    B, F = 4, 3
+    cfg = W.preset(1).replace(batch=B, d_model=64, n_heads=1, n_blocks=layers, n_ctx=2, n_frames=F, frame_h=1,
+                              frame_w=n_s, n_act=F, k_core=3, k_anchor=2, k_layer=k_layer)
+    ctx = swam.Context(cfg)
+    s = torch.exp(torch.randn((B, layers, F, n_s), generator=torch.Generator().manual_seed(3)) - 4.0).to("cuda:0")
+    bad = s.clone()
+    bad[1] = float("nan")
+    bad[3, layers // 2:] = float("nan")
+
+    def run(scores):
+        out = dict(v=torch.empty((B, F, n_s), device="cuda:0"), a=torch.empty((B, n_s), device="cuda:0"),
+                   q=torch.empty((B, layers), device="cuda:0"),
+                   core=torch.full((B, ctx.plan.k_layer_eff), -1, dtype=torch.int32, device="cuda:0"))
+        ctx.score_reduce(scores, out["v"], out["a"], q_out=out["q"], core_out=out["core"])
+        own_v = torch.empty_like(out["v"])
+        ctx.export(v=own_v)
+        torch.cuda.synchronize()
+        out["own_v"] = own_v
+        return {k: host(t) for k, t in out.items()}
+
+    want, got = run(s), run(bad)
+    for name in want:
+        for b in (0, 2):
+            np.testing.assert_array_equal(got[name][b], want[name][b], err_msg=f"{name}[{b}]")
+    for b in (1, 3):
+        assert np.isnan(got["v"][b]).all() and np.isnan(got["own_v"][b]).all()
+        core = got["core"][b]
+        assert (np.diff(core) > 0).all() and core[0] >= 0 and core[-1] < layers
