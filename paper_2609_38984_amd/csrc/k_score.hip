@@ -12,7 +12,7 @@
 // bf16: workgroup = 4 waves on 16 keys of one frame (score_unit.h); the MLP
 // up projection of a refresh step can run the same units in extra
 // workgroups of its own launch instead.
-// fp32: one wave per key, lanes = 16 queries x 4 quarters of the head dim.
+// fp32: lanes = the group's queries x keys x 4 quarters of the head dim.
 // Mode B normaliser: lambda over all keys of the sequence, per (query, head),
 // as an online max/sum split over key chunks with wavefront-shuffle
 // reductions, combined in a second pass.
@@ -27,6 +27,9 @@ __global__ void __launch_bounds__(256) score_bf16(const ScoreArgs a) {
                   (int)threadIdx.x, part, [] { __syncthreads(); });
 }
 
+// SLOTS: the group's queries rounded up to a power of two; a wave scores
+// 16 / SLOTS keys.  Lane (slot a, key, quarter dg of the head dim).
+template <int SLOTS>
 __global__ void __launch_bounds__(256)
 score_f32(const float* __restrict__ q, int64_t q_seq, int64_t q_row,
           const float* __restrict__ k, int64_t k_seq, int64_t k_row,
@@ -34,10 +37,10 @@ score_f32(const float* __restrict__ q, int64_t q_seq, int64_t q_row,
           int64_t s_seq, const float* __restrict__ alpha, int B, int F, int n_s, int H,
           int n_heads, int n_layers, int64_t q_lay, int64_t k_lay, int64_t lse_lay,
           int64_t s_lay) {
-  // one wave per key: lane (query slot a, quarter dg of the head dim)
-  const int64_t id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (id >= (int64_t)n_layers * B * F * n_s) return;
-  const int lane = threadIdx.x & 63, a = lane & 15, dg = lane >> 4;
+  const int lane = threadIdx.x & 63, a = lane & (SLOTS - 1), dg = lane >> 4;
+  const int64_t n = (int64_t)n_layers * B * F * n_s;
+  const int64_t own = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (16 / SLOTS) + (lane & 15) / SLOTS;
+  const int64_t id = min(own, n - 1);              // lanes past the last key join the exchange
   const int j = id % n_s, f = (id / n_s) % F, b = (id / ((int64_t)n_s * F)) % B;
   const int layer = (int)(id / ((int64_t)n_s * F * B));
   q += layer * q_lay;
@@ -58,14 +61,13 @@ score_f32(const float* __restrict__ q, int64_t q_seq, int64_t q_row,
     x += __shfl_xor(x, 32);
     // a padding slot repeats the last query: its term is left out, not weighted
     // by zero, so that an overflow there stays the infinity it is
-    if (a < g) s += aw * expf(x * 0.125f - lr[h]);
+    const float e = aw * expf(x * 0.125f - lr[h]);
+    s += a < g ? e : 0.0f;
   }
   // sum over the query slots (the four quarters hold the same sums)
-  s += __shfl_xor(s, 8);
-  s += __shfl_xor(s, 4);
-  s += __shfl_xor(s, 2);
-  s += __shfl_xor(s, 1);
-  if (lane == 0) s_out[(int64_t)b * s_seq + (int64_t)f * n_s + j] = s / (float)n_heads;
+#pragma unroll
+  for (int o = SLOTS / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (own < n && dg == 0 && a == 0) s_out[(int64_t)b * s_seq + (int64_t)f * n_s + j] = s / (float)n_heads;
 }
 
 // ---------------------------------------------------------------------------
@@ -128,6 +130,14 @@ __global__ void lse_combine(const float* __restrict__ part, int chunks, int B, i
   lse[id] = m + logf(s);
 }
 
+// fp32 keys from which a wave scores as many keys as the query group leaves it
+// lanes for.  Below, a wave per key keeps more of them in flight (us, a wave per
+// key | packed, one query per frame: 1,024 keys x 8 heads 5.2 | 7.1, 2,048 x 24
+// 13.7 | 16.0); from there on the idle lanes cost more (3,072 x 8 8.9 | 7.2,
+// 9,600 x 24 61.9 | 17.3, 16,384 x 16 64.2 | 13.3, and 47.9 with a thread per
+// key; eight queries 116.9 | 79.9).
+constexpr int64_t SCORE_KEYS = 3072;
+
 hipError_t launch_score(int dtype, const ScoreArgs& a, hipStream_t st) {
   const int nl = a.n_layers < 1 ? 1 : a.n_layers;
   if (dtype == 1) {
@@ -135,10 +145,21 @@ hipError_t launch_score(int dtype, const ScoreArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(score_bf16, dim3(nl * a.B * a.F * ktiles), dim3(256), 0, st, a);
   } else {
     const int64_t n = (int64_t)nl * a.B * a.F * a.n_s;
-    hipLaunchKernelGGL(score_f32, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st,
-                       (const float*)a.q, a.q_seq, a.q_row, (const float*)a.k, a.k_seq,
-                       a.k_row, a.lse, a.lse_seq, a.s_out, a.s_seq, a.alpha, a.B, a.F, a.n_s,
-                       a.H, a.n_heads, nl, a.q_lay, a.k_lay, a.lse_lay, a.s_lay);
+    const int g = a.H / a.F, slots = n < SCORE_KEYS ? 16 : g <= 1 ? 1 : g <= 2 ? 2 : g <= 4 ? 4 : g <= 8 ? 8 : 16;
+    const dim3 grid((unsigned)((n * slots + 63) / 64));
+#define SWAM_SCORE(SLOTS_)                                                                       \
+  hipLaunchKernelGGL(score_f32<SLOTS_>, grid, dim3(256), 0, st, (const float*)a.q, a.q_seq,      \
+                     a.q_row, (const float*)a.k, a.k_seq, a.k_row, a.lse, a.lse_seq, a.s_out,    \
+                     a.s_seq, a.alpha, a.B, a.F, a.n_s, a.H, a.n_heads, nl, a.q_lay, a.k_lay,    \
+                     a.lse_lay, a.s_lay)
+    switch (slots) {
+      case 1: SWAM_SCORE(1); break;
+      case 2: SWAM_SCORE(2); break;
+      case 4: SWAM_SCORE(4); break;
+      case 8: SWAM_SCORE(8); break;
+      default: SWAM_SCORE(16); break;
+    }
+#undef SWAM_SCORE
   }
   return hipGetLastError();
 }

@@ -62,10 +62,11 @@ def test_logit_of_minus_infinity(heads, cu, dtype):
     assert maxrel(host(y), want) < TOL[dtype]
 
 
-@pytest.mark.parametrize("heads,n_s", [(1, 5), (3, 17), (2, 64)])
+@pytest.mark.parametrize("heads,n_s", [(1, 5), (3, 17), (2, 64), (1, 683), (2, 690)])
 @pytest.mark.parametrize("g", [1, 2, 3, 4, 5, 8, 11, 16])
 def test_fp32_scores_and_their_overflow(g, heads, n_s):
-    """fp32 scores of every size of the query group, as the oracle's; with a
+    """fp32 scores of every size of the query group, as the oracle's, on both
+    sides of 3,072 keys (a wave per key, several keys to a wave); with a
     normaliser so low that the last query of the first frame overflows, that
     frame's scores are infinite, not NaN, and the others unchanged."""
     from paper_2609_38984_amd import swam
