@@ -77,8 +77,20 @@ hipError_t launch_adaln(int dtype, const AdalnArgs& a, int n_blk, const float* t
 // 11.4, down 13.0 / 9.7, out 6.4 / 5.5; attention takes 2.1 us and LayerNorm 1.0
 // us longer.  Spare workgroups in the projections themselves cost them more than
 // they save: up 15.8 us).
+// Only while a block's four matrices are at most READ_AHEAD_BYTES: a launch ends
+// with its read, so what it reads has to fit into the time it would take alone.
+// us per block with | without, weights from memory, 48 / 192 / 1,024 rows: d =
+// 1,024 (25 MB) 38.5 | 42.2, 44.2 | 48.7, 76.0 | 78.0; 1,536 (57 MB) 48.7 | 51.5,
+// 59.1 | 66.0, 124.6 | 138.8; 2,816 with an MLP ratio of 1 (95 MB; 64 rows first)
+// 66.5 | 67.9, 80.2 | 86.4, 174.5 | 187.8; 2,048 (101 MB) 61.3 | 59.9, 81.5 | 82.3,
+// 175.1 | 174.6; 3,072 (226 MB) 100.3 | 89.2, 139.9 | 129.9, 340.0 | 328.2; 4,096
+// (403 MB) 153.5 | 122.5, 218.6 | 179.3, 519.5 | 486.4.  Reading only the first 6 to
+// 36 MB of each launch's weights gained nothing above the line (2,048: 1-4% slower
+// than none).  Weights that the caches already hold (a model of two blocks) cost
+// 0-5% of a block up to d = 1,536.
 constexpr int SHORT_ROWS = 1024;
 constexpr int PREFETCH_WGS = 256;
+constexpr int64_t READ_AHEAD_BYTES = 96000000;
 
 // h[r] = LN(x[r]) (1 + scale) + shift; pf: see above (bf16, up to SHORT_ROWS rows)
 hipError_t launch_ln_mod(int dtype, const void* x, void* h, const float* shift,

@@ -332,7 +332,8 @@ int run_block(swam_ctx* c, const swam_block_weights* w, const float* mod, void* 
   const float *sh2 = mod + 3 * d, *sc2 = mod + 4 * d, *g2 = mod + 5 * d;
   if (n_rows <= 0) return SWAM_OK;
   // short token sets read the next projections' weights ahead of them
-  const bool ahead = dt == SWAM_BF16 && n_rows <= SHORT_ROWS;
+  const bool ahead = dt == SWAM_BF16 && n_rows <= SHORT_ROWS &&
+                     (4 * d + 2 * hid) * d * c->dv.esz <= READ_AHEAD_BYTES;
   auto read_ahead = [&](const void* p, int64_t elems) {
     return ahead && p ? Prefetch{p, elems * c->dv.esz} : Prefetch{};
   };
