@@ -17,6 +17,8 @@
 // pack is a coalesced 16-byte row gather, unpack the matching scatter.
 #include "launchers.h"
 
+#include <algorithm>
+
 namespace swam {
 
 constexpr int SEL_THREADS = 1024;
@@ -235,13 +237,15 @@ reduce_frames(const float* __restrict__ s_all, int n_s, double* __restrict__ fsu
   }
 }
 
-// Layer qualities, core layers, V and A: one workgroup per (b, 64 positions),
-// one wave per frame (waves take frames w, w + nw, ...).  Every workgroup forms
+// Layer qualities, core layers, V and A: one workgroup per (b, POS positions),
+// 64 / POS frames per wave at a time.  Every workgroup forms
 // the L qualities of its sequence from the frame sums (a few hundred float64)
 // instead of waiting for a launch that does; V_all of its positions meets in
 // LDS for the mean and deviation over frames.  All sums are float64 in layer
 // (frame) order, rounded once.  28 layers of 8 x 1,200: 10.9 us, against
 // 5.8 + 6.2 + 3.9 us and two launch gaps for layers, positions and anchors apart.
+// LOOP: the workgroup goes on to its sequence's next free POS positions.
+template <int POS, bool LOOP>
 __global__ void __launch_bounds__(1024)
 reduce_maps(const float* __restrict__ s_all, const double* __restrict__ fsum,
             const double* __restrict__ fent, int L, int F, int n_s, int k_eff, float cv,
@@ -251,7 +255,7 @@ reduce_maps(const float* __restrict__ s_all, const double* __restrict__ fsum,
   __shared__ float q32[64];
   __shared__ int flag[64];
   __shared__ double dens[2];
-  __shared__ double vall[64][64];                // [frame][position]
+  __shared__ double vall[64][POS];               // [frame][position]
   const int b = blockIdx.y, tid = threadIdx.x;
   if (tid < L) {
     double tot = 0.0, ent = 0.0;
@@ -301,35 +305,39 @@ reduce_maps(const float* __restrict__ s_all, const double* __restrict__ fsum,
     if (da == 0.0) qv[tid] = 1.0;
   }
   __syncthreads();
-  const int lane = tid & 63, nw = blockDim.x >> 6;
-  const int j = blockIdx.x * 64 + lane;
+  const int pos = tid % POS, nf = blockDim.x / POS;
   const int64_t ls = (int64_t)F * n_s;           // layer stride
-  for (int f = tid >> 6; f < F; f += nw) {
-    const float* sb = s_all + (int64_t)b * L * ls + (int64_t)f * n_s + min(j, n_s - 1);
-    double acc = 0.0, all = 0.0;
+  for (int j0 = blockIdx.x * POS; j0 < n_s; j0 += gridDim.x * POS) {
+    const int j = j0 + pos;
+    for (int f = tid / POS; f < F; f += nf) {
+      const float* sb = s_all + (int64_t)b * L * ls + (int64_t)f * n_s + min(j, n_s - 1);
+      double acc = 0.0, all = 0.0;
 #pragma unroll 8
-    for (int l = 0; l < L; ++l) {
-      const double sv = (double)sb[l * ls];
-      if (flag[l]) acc += wc[l] * sv;
-      all += qv[l] * sv;
+      for (int l = 0; l < L; ++l) {
+        const double sv = (double)sb[l * ls];
+        if (flag[l]) acc += wc[l] * sv;
+        all += qv[l] * sv;
+      }
+      acc /= dc != 0.0 ? dc : (double)k_eff;
+      all /= da != 0.0 ? da : (double)L;
+      if (j < n_s) v_out[((int64_t)b * F + f) * n_s + j] = (float)acc;
+      vall[f][pos] = all;
     }
-    acc /= dc != 0.0 ? dc : (double)k_eff;
-    all /= da != 0.0 ? da : (double)L;
-    if (j < n_s) v_out[((int64_t)b * F + f) * n_s + j] = (float)acc;
-    vall[f][lane] = all;
-  }
-  __syncthreads();
-  if (tid < 64 && j < n_s) {
-    double mu = 0.0;
-    for (int f = 0; f < F; ++f) mu += vall[f][lane];
-    mu /= F;
-    double var = 0.0;
-    for (int f = 0; f < F; ++f) {
-      const double dv = vall[f][lane] - mu;
-      var += dv * dv;
+    __syncthreads();
+    if (tid < POS && j < n_s) {
+      double mu = 0.0;
+      for (int f = 0; f < F; ++f) mu += vall[f][pos];
+      mu /= F;
+      double var = 0.0;
+      for (int f = 0; f < F; ++f) {
+        const double dv = vall[f][pos] - mu;
+        var += dv * dv;
+      }
+      const double sd = sqrt(var / F);
+      a_out[(int64_t)b * n_s + j] = mu != 0.0 ? (float)(mu / (1.0 + (double)cv * (sd / mu))) : 0.0f;
     }
-    const double sd = sqrt(var / F);
-    a_out[(int64_t)b * n_s + j] = mu != 0.0 ? (float)(mu / (1.0 + (double)cv * (sd / mu))) : 0.0f;
+    if constexpr (!LOOP) break;
+    __syncthreads();                             // vall is free for the next positions
   }
 }
 
@@ -375,17 +383,36 @@ hipError_t launch_overlap(const float* p, const float* q, int64_t n_maps, int64_
   return hipGetLastError();
 }
 
+template <int POS, bool LOOP>
+static hipError_t run_reduce_maps(const ReduceArgs& a, int k_eff, int wgs, int waves, hipStream_t st) {
+  hipLaunchKernelGGL((reduce_maps<POS, LOOP>), dim3(wgs, a.B), dim3(64 * waves), 0, st, a.s_all,
+                     a.frame_sum, a.frame_ent, a.L, a.F, a.n_s, k_eff, a.cv_penalty, a.q, a.core,
+                     a.v, a.a);
+  return hipGetLastError();
+}
+
 hipError_t launch_score_reduce(const ReduceArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(reduce_frames, dim3(a.B * a.L * a.F), dim3(256), 0, st, a.s_all, a.n_s,
                      a.frame_sum, a.frame_ent);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int k_eff = a.k_layer < a.L ? a.k_layer : a.L;
-  const int nw = a.F < 16 ? a.F : 16;
-  hipLaunchKernelGGL(reduce_maps, dim3((a.n_s + 63) / 64, a.B), dim3(64 * nw), 0, st, a.s_all,
-                     a.frame_sum, a.frame_ent, a.L, a.F, a.n_s, k_eff, a.cv_penalty, a.q, a.core,
-                     a.v, a.a);
-  return hipGetLastError();
+  // 16 waves cover 16 frames of 64 positions or 32 of 32 at a time.  More than 16
+  // frames are taken in turn, which only pays where workgroups of 64 positions
+  // fill the CUs (us, both launches, 32 | 64 positions | layers,
+  // positions and anchors apart: 64 layers of 64 x 1,024 72.0 | 105.5 | 78.0, of
+  // 64 x 4,096 117 | 155 | 130, 28 of 32 x 4,096 33.9 | 42.6 | 48.6; 4 sequences
+  // of 28 layers of 64 x 4,096 158 | 150 | 172, 8 of 28 of 8 x 1,200 24.5 | 23.6 |
+  // 30.8).
+  const int tiles = (a.n_s + 63) / 64;
+  if (a.F > 16 && tiles * a.B < 256)
+    return run_reduce_maps<32, false>(a, k_eff, (a.n_s + 31) / 32, std::min((a.F + 1) / 2, 16), st);
+  // no more workgroups than the CUs hold at a time (32 waves, and four by their
+  // LDS): a second round would form the qualities again, so workgroups loop over
+  // positions instead (64 sequences of 12 layers of 16 x 1,024: 86.4 -> 82.2 us)
+  const int waves = std::min(a.F, 16), share = (256 * std::min(4, 32 / waves) + a.B - 1) / a.B;
+  if (tiles > share) return run_reduce_maps<64, true>(a, k_eff, share, waves, st);
+  return run_reduce_maps<64, false>(a, k_eff, tiles, waves, st);
 }
 
 // ---------------------------------------------------------------------------
