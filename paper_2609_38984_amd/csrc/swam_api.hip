@@ -519,7 +519,14 @@ struct CopyOut {
   void add(void* dst, size_t src_off, int64_t bytes) {
     if (dst) list.add(c->arena + src_off, dst, bytes);
   }
-  int run(const char* what) { return hip_check(c, launch_copy_list(list, c->st), what); }
+  int run(const char* what) {
+    // one buffer: the runtime's own copy is enqueued faster, which is what a call
+    // takes up to some 16 MB (5.8 us against 6.3); 268 MB 99.5 us against 91.2
+    if (list.n == 1 && list.bytes[0] <= 16 << 20)
+      return hip_check(c, hipMemcpyAsync(list.dst[0], list.src[0], list.bytes[0],
+                                         hipMemcpyDeviceToDevice, c->st), what);
+    return hip_check(c, launch_copy_list(list, c->st), what);
+  }
 };
 
 void fill_alpha(int g, float* out) {
