@@ -37,7 +37,7 @@ TOL = {"bf16": 2e-2, "f32": 1e-4}
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("variant", [dict(), dict(rope=1, qk_norm=1)])
 @pytest.mark.parametrize("heads,rows", [(1, 3), (1, 64), (2, 65), (3, 127), (5, 129), (8, 192), (7, 193), (17, 321),
-                                        (24, 192), (12, 700)])
+                                        (24, 192), (12, 700), (5, 2049)])   # (the last: QKV on 128x64 tiles)
 def test_block_short_rows(heads, rows, variant, dtype):
     from paper_2609_38984_amd import swam
     cfg = _cfg(heads, rows, dtype=dtype, **variant)
@@ -60,11 +60,14 @@ def test_block_short_rows(heads, rows, variant, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("heads,rows", [(1, 70), (9, 130), (24, 192), (33, 100)])
+@pytest.mark.parametrize("heads,rows", [(1, 70), (9, 130), (24, 192), (33, 100), (9, 1151), (3, 2689), (11, 2689)])
 def test_step_chains_the_layer_norms(heads, rows, dtype):
     """Dense steps of 3 blocks: the next block's first LayerNorm comes out of
     the pass that sums the split down projection (33 heads: two chunks of a row
-    per thread there)."""
+    per thread there).  The last three run 128x64 tiles at the edges of 128
+    rows: split down projections in bf16 (9 heads) and fp32 (3 heads), a split
+    out projection in fp32 (9 heads), out and down without a split in both (11
+    heads)."""
     from paper_2609_38984_amd import swam
     cfg = _cfg(heads, rows, dtype=dtype).replace(n_blocks=3)
     blocks, _, model = model_for(cfg)
