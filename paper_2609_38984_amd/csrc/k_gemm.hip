@@ -645,8 +645,8 @@ hipError_t launch_gemm_qkv(int dtype, const void* A, int64_t lda, const void* B,
   const hipError_t e = launch_gemm(dtype, ROLE_QKV, A, lda, B, ldb, bias, nullptr, C, ldc, M, N, K,
                                    st, ws, ws_floats);
   if (e != hipSuccess || !post) return e;
-  return launch_qk_post(dtype, C, M, qp.d, qp.pos_mode, qp.gather, qp.cu, qp.n_seqs, qp.l_full,
-                        qp.tab, qp.n_pos, qp.qk_norm, st);
+  return launch_qk_post((float*)C, M, qp.d, qp.pos_mode, qp.gather, qp.cu, qp.n_seqs, qp.l_full, qp.tab,
+                        qp.n_pos, qp.qk_norm, st);
 }
 
 }  // namespace swam

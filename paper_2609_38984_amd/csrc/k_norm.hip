@@ -347,13 +347,13 @@ hipError_t launch_rope_table(float2* tab, int n_pos, hipStream_t st) {
   return hipGetLastError();
 }
 
+// fp32 (the bf16 projections' store does the same: qkpost_store):
 // one thread per 8 consecutive elements of q or k (a head is 8 threads, which
 // are 8 consecutive lanes); pos_mode 0: row % l_full, 1: gather[row] % l_full,
 // 2: row - cu[b] for the row's sequence b; positions are clamped to the
 // table's n_pos rows
-template <typename T>
 __global__ void __launch_bounds__(256)
-qk_post_kernel(T* __restrict__ qkv, int64_t n_rows, int d, int pos_mode,
+qk_post_kernel(float* __restrict__ qkv, int64_t n_rows, int d, int pos_mode,
                const int32_t* __restrict__ gather, const int32_t* __restrict__ cu, int n_seqs,
                int l_full, const float2* __restrict__ tab, int n_pos, int qk_norm) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -361,20 +361,9 @@ qk_post_kernel(T* __restrict__ qkv, int64_t n_rows, int d, int pos_mode,
   const bool live = id < n_rows * chunks;
   const int64_t row = live ? id / chunks : 0;
   const int c8 = live ? (int)(id % chunks) * 8 : 0;
-  T* p = qkv + row * 3 * d + c8;
+  float* p = qkv + row * 3 * d + c8;
   float x[8];
-  if constexpr (sizeof(T) == 2) {
-    const uint4 u = *reinterpret_cast<const uint4*>(p);
-    const uint32_t wv[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      x[2 * e] = __uint_as_float(wv[e] << 16);
-      x[2 * e + 1] = __uint_as_float(wv[e] & 0xFFFF0000u);
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = p[e];
-  }
+  load8(p, x);
   if (qk_norm) {
     // the 8 lanes of a head are consecutive and aligned (chunks per row and per
     // head are multiples of 8); every lane takes part in the exchange
@@ -410,27 +399,16 @@ qk_post_kernel(T* __restrict__ qkv, int64_t n_rows, int d, int pos_mode,
       x[2 * e + 1] = a * cs.y + b * cs.x;
     }
   }
-  if constexpr (sizeof(T) == 2) {
-    *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]),
-                                              pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) p[e] = x[e];
-  }
+  store8(p, x);
 }
 
-hipError_t launch_qk_post(int dtype, void* qkv, int64_t n_rows, int d, int pos_mode,
-                          const int32_t* gather, const int32_t* cu, int n_seqs, int l_full,
-                          const float2* tab, int n_pos, int qk_norm, hipStream_t st) {
+hipError_t launch_qk_post(float* qkv, int64_t n_rows, int d, int pos_mode, const int32_t* gather,
+                          const int32_t* cu, int n_seqs, int l_full, const float2* tab, int n_pos,
+                          int qk_norm, hipStream_t st) {
   if (n_rows <= 0) return hipSuccess;
   const int64_t n = n_rows * (2 * d / 8);
-  const dim3 grid((unsigned)((n + 255) / 256));
-  if (dtype == 1)
-    hipLaunchKernelGGL(qk_post_kernel<bf16_t>, grid, dim3(256), 0, st, (bf16_t*)qkv, n_rows, d,
-                       pos_mode, gather, cu, n_seqs, l_full, tab, n_pos, qk_norm);
-  else
-    hipLaunchKernelGGL(qk_post_kernel<float>, grid, dim3(256), 0, st, (float*)qkv, n_rows, d,
-                       pos_mode, gather, cu, n_seqs, l_full, tab, n_pos, qk_norm);
+  hipLaunchKernelGGL(qk_post_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, qkv, n_rows, d,
+                     pos_mode, gather, cu, n_seqs, l_full, tab, n_pos, qk_norm);
   return hipGetLastError();
 }
 

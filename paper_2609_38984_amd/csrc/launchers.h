@@ -54,9 +54,9 @@ hipError_t launch_gemm(int dtype, int role, const void* A, int64_t lda, const vo
                        const int32_t* smap = nullptr, LnNext* ln = nullptr);
 
 // QKV projection C = A . B^T + bias followed by the QK-norm / rotary
-// embedding of qp on its q and k columns, with the same bf16 rounding of the
-// projection as launch_gemm + launch_qk_post; fused into the GEMM's store
-// for bf16 (which then does not split K), two launches for fp32.
+// embedding of qp on its q and k columns: in the GEMM's store for bf16 (on the
+// projection rounded to bf16; it then does not split K), a second launch for
+// fp32.
 hipError_t launch_gemm_qkv(int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                            const void* bias, void* C, int64_t ldc, int64_t M, int64_t N,
                            int64_t K, const QkPost& qp, hipStream_t st, float* ws = nullptr,
@@ -110,11 +110,11 @@ hipError_t launch_ln_mod_gather(int dtype, const void* x_full, const int32_t* ga
                                 void* h, const float* shift, const float* scale, int64_t rows,
                                 int d, hipStream_t st);
 
-// backbone variants: rotary table and QK-norm / RoPE of the stored q and k
+// backbone variants: rotary table and QK-norm / RoPE of the stored q and k (fp32)
 hipError_t launch_rope_table(float2* tab, int n_pos, hipStream_t st);
-hipError_t launch_qk_post(int dtype, void* qkv, int64_t n_rows, int d, int pos_mode,
-                          const int32_t* gather, const int32_t* cu, int n_seqs, int l_full,
-                          const float2* tab, int n_pos, int qk_norm, hipStream_t st);
+hipError_t launch_qk_post(float* qkv, int64_t n_rows, int d, int pos_mode, const int32_t* gather,
+                          const int32_t* cu, int n_seqs, int l_full, const float2* tab, int n_pos,
+                          int qk_norm, hipStream_t st);
 
 // o = softmax(q k^T / 8) v per head inside each sequence; lse (optional).
 // Sequence bounds are clamped to [0, n_rows].  pf0, pf1 (bf16): weights read ahead.
