@@ -61,8 +61,8 @@ score_f32(const float* __restrict__ q, int64_t q_seq, int64_t q_row,
     x += __shfl_xor(x, 32);
     // a padding slot repeats the last query: its term is left out, not weighted
     // by zero, so that an overflow there stays the infinity it is
-    const float e = aw * expf(x * 0.125f - lr[h]);
-    s += a < g ? e : 0.0f;
+    const float t = fmaf(aw, expf(x * 0.125f - lr[h]), s);
+    s = a < g ? t : s;
   }
   // sum over the query slots (the four quarters hold the same sums)
 #pragma unroll
