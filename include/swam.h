@@ -139,7 +139,9 @@ typedef struct {
   int64_t k_max;          /* max retained per frame (K_c+K_s, or N_s in mass mode) */
   int64_t t_pack_fixed;   /* packed rows per sequence in fixed mode, else -1 */
   int64_t k_layer_eff;    /* min(k_layer, n_blocks) */
-  int64_t workspace_bytes;/* device bytes swam_create allocates */
+  int64_t workspace_bytes;/* device bytes swam_create allocates (both dtypes: with
+                             room for the fp32 partial sums of projections that
+                             split K, at most 128 MB) */
 } swam_plan_info;
 
 /* Weights of one block; each matrix is [out_features][in_features] row-major,

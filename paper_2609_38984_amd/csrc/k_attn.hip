@@ -48,8 +48,8 @@ typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 // query rows, each with its own stage buffers; their (max, sum, O) are merged
 // through LDS in group order.  A workgroup alone on its CU is bound by the
 // serial chain over its key tiles (one wave per SIMD hides neither the LDS
-// reads nor the exponentials), so half the chain is worth the merge: 1,312
-// rows x 16 heads 21.7 -> 18.5 us, 2,686 x 12 40.4 -> 33.1; four groups: 20.9.
+// reads nor the exponentials), so half the chain is worth the merge; four groups
+// are slower again (1,312 rows x 16 heads, 13%).  The launcher has the figures.
 template <int NW, int WPE, int SUB, int KS>
 __global__ void __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
 attn_fwd_bf16(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,

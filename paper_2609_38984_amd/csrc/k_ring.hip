@@ -7,7 +7,8 @@
 // flight per workgroup.  Here the A and B tiles of NST k-stages of 64 form a
 // ring in LDS; the DMA loads of stage kt + NST - 1 are issued before stage kt
 // is multiplied and a counted vmcnt wait leaves the NST - 2 younger stages in
-// flight, so 48-128 KB per CU are on their way at any time.
+// flight: 48-64 KB per workgroup are on their way while a stage is multiplied
+// (up to 96 KB on a CU that holds two workgroups), 24-32 KB during the wait.
 //
 // Tile (64 WM) x (64 WN): every wave holds a 64 x 64 accumulator block (four
 // 32x32x16 MFMAs per 16 columns of K) and the WK waves of one block take

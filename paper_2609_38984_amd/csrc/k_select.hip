@@ -460,7 +460,11 @@ __device__ __forceinline__ uint64_t mass_code(float x) {
 
 // fixed budgets: cores of one frame per workgroup, the top K_c of V(f, .) in P;
 // the pool (the same in every frame of a sequence) is formed by each of them:
-// 8 x 1,200 positions take 13.0 us, against 11.3 + 8.2 us and a launch gap apart
+// 8 x 1,200 positions take 13.0 us, against 11.3 + 8.2 us and a launch gap apart.
+// That reads F^2 N_s scores per sequence: 71.6 us at 64 x 4,096 (68.3 + 11.0
+// apart), 42.6 for 8 sequences of 64 x 1,024 (43.6 + 10.2); only where the frames
+// outnumber what the CUs hold several times over is the pool alone the shorter
+// way, 32 sequences of 64 x 4,096 (502 us, 74 + 53 apart).
 __global__ void __launch_bounds__(SEL_THREADS)
 select_core_fixed(const float* __restrict__ v, int F, int n_s, int k_core, int k_anchor,
                   uint8_t* __restrict__ core) {
