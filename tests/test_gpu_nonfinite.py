@@ -1,6 +1,7 @@
 """Infinite and NaN values on the GPU where they have a defined effect: a key
 whose logit overflows to minus infinity takes no part in the softmax of its
-sequence, wherever the attention's key tiles and waves put it."""
+sequence, wherever the attention's key tiles and waves put it; an fp32 score
+that overflows is infinite; layers of NaN quality stay in their sequence."""
 import numpy as np
 import pytest
 import torch
